@@ -8,6 +8,8 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -15,14 +17,13 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libjc.so")
 
-SOURCES = ["jc_kernels.hip", "jc_synth.hip", "jc_host.cpp", "jc_group.cpp"]
+SOURCES = ["jc_kernels.hip", "jc_rows.hip", "jc_synth.hip", "jc_host.cpp", "jc_group.cpp"]
 
 FLAGS = [
     "--offload-arch=gfx950",
     "-O3",
     "-std=c++17",
     "-fPIC",
-    "-shared",
     # bitwise parity: no fused multiply-add contraction anywhere
     "-ffp-contract=off",
     "-fno-fast-math",
@@ -39,13 +40,21 @@ def hipcc() -> str:
 
 
 def build(verbose: bool = False) -> str:
-    """Compile every source into libjc.so (always recompiles)."""
-    srcs = [os.path.join(CSRC, s) for s in SOURCES]
+    """Compile every source (in parallel) into libjc.so (always recompiles)."""
     tmp = LIB + ".tmp%d" % os.getpid()
-    cmd = [hipcc()] + FLAGS + ["-I", INCLUDE, "-I", CSRC, "-o", tmp] + srcs
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.check_call(cmd)
+
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.check_call(cmd)
+
+    with tempfile.TemporaryDirectory() as objdir:
+        objs = [os.path.join(objdir, os.path.splitext(s)[0] + ".o") for s in SOURCES]
+        with ThreadPoolExecutor(max_workers=8) as pool:
+            for _ in pool.map(lambda so: run([hipcc()] + FLAGS + ["-I", INCLUDE, "-I", CSRC, "-c", "-o", so[1],
+                                                                  os.path.join(CSRC, so[0])]), zip(SOURCES, objs)):
+                pass
+        run([hipcc(), "--offload-arch=gfx950", "-shared", "-o", tmp] + objs)
     os.replace(tmp, LIB)
     return LIB
 

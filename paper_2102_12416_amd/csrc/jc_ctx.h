@@ -207,6 +207,13 @@ struct jc_ctx {
             m = b.n[1] * b.n[2] > m ? b.n[1] * b.n[2] : m;
         return m;
     }
+    int64_t max_nx() const
+    {
+        int64_t m = 1;
+        for (const HostBlock& b : blocks)
+            m = b.n[0] > m ? b.n[0] : m;
+        return m;
+    }
     int np() const { return (int)pairs.size(); }
 };
 

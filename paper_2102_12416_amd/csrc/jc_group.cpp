@@ -34,7 +34,7 @@ struct Class {
     bool src = false;    // members with a source
     int lo = JC_F64;     // refinement storage
     int bstart = 0, bend = 0;        // joint block range
-    int64_t max_rows = 1;            // largest ny * nz of the class's blocks
+    int64_t max_rows = 1, max_nx = 1;    // largest ny * nz and nx of the class's blocks
     size_t item0 = 0;                // first joint item
     std::vector<Item> items;
     size_t item2_0 = 0;              // first joint two-sweep item
@@ -153,7 +153,8 @@ int group_sweep(jc_group* g)
             const jc_ctx* c0 = g->members[k.members[0]];
             hipError_t e;
             if (c0->ir_phase == 1)
-                e = jc::launch_ir_first(g->d_desc() + k.bstart, k.bend - k.bstart, k.max_rows, k.lo, g->stream);
+                e = jc::launch_ir_first(g->d_desc() + k.bstart, k.bend - k.bstart, k.max_rows, k.max_nx, k.lo,
+                                        g->stream);
             else
                 e = jc::launch_ir_inner(g->d_desc(), g->d_items() + k.item0, n, c0->ir_q, g->tile[0], g->tile[1], k.lo,
                                         g->stream);
@@ -377,6 +378,7 @@ int jc_group_create(jc_ctx* const* ctxs, int n, void* hip_stream, int flags, con
             const jc_ctx* c = ctxs[m];
             g->member_bstart[m] = (int)g->desc.size();
             k.max_rows = std::max(k.max_rows, c->max_rows());
+            k.max_nx = std::max(k.max_nx, c->max_nx());
             const size_t i0 = g->items.size();
             const size_t first = k.items.size();
             member_items(c, g->tile, (int)g->desc.size(), m, k.items);
@@ -699,20 +701,34 @@ int jc_group_residuals(jc_group* g, double* host_l2)
         }
         for (int m : k.members) {
             jc_ctx* c = g->members[m];
-            const int nb = (int)c->blocks.size();
-            BlockDesc* bd = g->d_desc() + g->member_bstart[m];
             if (!c->ir_zeroed) {
                 st = ghip(jc::launch_zero(c->arena + c->lo_begin, c->lo_end - c->lo_begin, g->stream), "zero");
                 if (st != JC_OK)
                     return st;
                 c->ir_zeroed = true;
             }
+        }
+        // outer update with the correction of the sweeps just run: one launch
+        // per run of members (neighbours in the joint block table) whose
+        // correction is in the same copy, normally the whole class
+        for (size_t i = 0; i < k.members.size();) {
+            const jc_ctx* c = g->members[k.members[i]];
+            const int b0 = g->member_bstart[k.members[i]];
+            int b1 = b0;
+            size_t j = i;
+            for (; j < k.members.size(); ++j) {
+                const jc_ctx* o = g->members[k.members[j]];
+                if (o->ir_phase != c->ir_phase || o->ir_q != c->ir_q || o->parity != c->parity)
+                    break;
+                b1 = g->member_bstart[k.members[j]] + o->nb();
+            }
             if (c->ir_phase == 2) {
-                // outer update with the correction of the sweeps just run
-                st = ghip(jc::launch_ir_update(bd, nb, c->max_rows(), c->parity, c->ir_q, k.lo, g->stream), "update");
+                st = ghip(jc::launch_ir_update(g->d_desc() + b0, b1 - b0, k.max_rows, k.max_nx, c->parity, c->ir_q,
+                                               k.lo, g->stream), "update");
                 if (st != JC_OK)
                     return st;
             }
+            i = j;
         }
         // refining members keep their iterate in copy 0 (their items' flip is 0)
         const hipError_t e = jc::launch_ir_residual(g->d_desc(), g->d_items() + k.item0, n, 0, g->tile[0], g->tile[1],

@@ -1230,9 +1230,8 @@ int jc_load_field(jc_ctx* c, int which, const void* src)
         return fail(JC_ERR_INVALID, "context was created without a source field");
     if (which != JC_FIELD_U && which != JC_FIELD_B)
         return fail(JC_ERR_INVALID, "which must be JC_FIELD_U or JC_FIELD_B");
-    JC_HIP(jc::launch_scatter(c->d_blocks(), c->nb(), c->max_rows(), static_cast<const double*>(src), c->grid[0],
-                              c->grid[1],
-                              which, c->stream));
+    JC_HIP(jc::launch_scatter(c->d_blocks(), c->nb(), c->max_rows(), c->max_nx(), static_cast<const double*>(src),
+                              c->grid[0], c->grid[1], which, c->stream));
     if (which == JC_FIELD_U) {
         c->loaded_u = true;
         c->check_r0 = -1.0;
@@ -1261,8 +1260,8 @@ int jc_store_field(jc_ctx* c, int which, void* dst)
         return fail(JC_ERR_INVALID, "which must be JC_FIELD_U or JC_FIELD_B");
     if ((which == JC_FIELD_U && !c->loaded_u) || (which == JC_FIELD_B && !c->loaded_b))
         return fail(JC_ERR_STATE, "field was never loaded");
-    JC_HIP(jc::launch_gather(c->d_blocks(), c->nb(), c->max_rows(), static_cast<double*>(dst), c->grid[0], c->grid[1],
-                             c->grid[2], which, c->parity, c->stream));
+    JC_HIP(jc::launch_gather(c->d_blocks(), c->nb(), c->max_rows(), c->max_nx(), static_cast<double*>(dst),
+                             c->grid[0], c->grid[1], c->grid[2], which, c->parity, c->stream));
     return JC_OK;
 }
 
@@ -1491,7 +1490,7 @@ int jc_solve_ir(jc_ctx* c, int inner_sweeps, double rtol, int64_t max_inner, jc_
         const int q = ir_final_copy(c, m);
         auto inner_window = [&]() -> int {
             int s2 = timed(c, JC_K_IR_INNER, [&] {
-                return jc::launch_ir_first(c->d_blocks(), c->nb(), c->max_rows(), lo, c->stream);
+                return jc::launch_ir_first(c->d_blocks(), c->nb(), c->max_rows(), c->max_nx(), lo, c->stream);
             });
             int qq = 1;
             int64_t j = 1;
@@ -1547,7 +1546,8 @@ int jc_solve_ir(jc_ctx* c, int inner_sweeps, double rtol, int64_t max_inner, jc_
                 return st;
         }
         st = timed(c, JC_K_IR_OUTER, [&] {
-            return jc::launch_ir_update(c->d_blocks(), c->nb(), c->max_rows(), c->parity, q, lo, c->stream);
+            return jc::launch_ir_update(c->d_blocks(), c->nb(), c->max_rows(), c->max_nx(), c->parity, q, lo,
+                                        c->stream);
         });
         if (st != JC_OK)
             return st;

@@ -20,6 +20,7 @@
 
 #include "jc_div6.h"
 #include "jc_kernels.h"
+#include "jc_storage.h"
 
 namespace jc {
 
@@ -34,141 +35,7 @@ __device__ __forceinline__ int logical_block(int bid, int nblocks)
     return (bid & 7) * per + (bid >> 3);
 }
 
-// Global-memory views of the generic pointers held in the tables: loads
-// and stores through them are global (not flat) instructions, which count
-// only against the vector-memory counter, so waiting for an LDS write does
-// not also wait for every load still in flight.
-#define JC_GLOBAL __attribute__((address_space(1)))
-
 // ---- sweep kernel: begin (its source is fingerprinted with recorded counters) ----
-typedef double v2d __attribute__((ext_vector_type(2)));
-typedef float v2f __attribute__((ext_vector_type(2)));
-
-// bfloat16: the upper half of a binary32, rounded to nearest even
-__device__ __forceinline__ float bf16_to_f32(uint32_t h)
-{
-    return __uint_as_float(h << 16);
-}
-
-// Round to nearest even without a branch: adding 0x7fff plus the kept
-// half's lowest bit carries into the upper half exactly when the dropped
-// half is above one half, or equal to it with an odd kept half (equal, bit
-// for bit, to the comparison form for every binary32 pattern).  A NaN
-// stays a (quiet) NaN.
-__device__ __forceinline__ uint32_t f32_to_bf16(float f)
-{
-    const uint32_t x = __float_as_uint(f);
-    const uint32_t rounded = (x + 0x7fffu + ((x >> 16) & 1u)) >> 16;
-    const uint32_t quiet_nan = (x >> 16) | 0x40u;
-    return __builtin_isnan(f) ? quiet_nan : rounded;   // an unordered self-compare
-}
-
-// Storage formats of a swept field: arithmetic type C, and loads / stores
-// of the 2-element aligned pair (x, x + 1) that one thread owns.
-template <typename T> struct Tr;
-
-template <> struct Tr<double> {
-    using C = double;
-    __device__ static void ld(const double* p, double& a, double& b)
-    {
-        const v2d v = *(const v2d JC_GLOBAL*)(p);
-        a = v.x;
-        b = v.y;
-    }
-    __device__ static void st(double* p, double a, double b)
-    {
-        v2d v;
-        v.x = a;
-        v.y = b;
-        *(v2d JC_GLOBAL*)(p) = v;
-    }
-    __device__ static void st1(double* p, double a) { *(double JC_GLOBAL*)(p) = a; }
-    // streaming store: the new iterate is not read again before the next
-    // sweep, so it should not displace lines the current sweep re-reads
-    __device__ static void stn(double* p, double a, double b)
-    {
-        v2d v;
-        v.x = a;
-        v.y = b;
-        __builtin_nontemporal_store(v, (v2d JC_GLOBAL*)(p));
-    }
-    // a pair converted to storage once, stored whole or by element
-    using P = v2d;
-    __device__ static P pack(double a, double b)
-    {
-        v2d v;
-        v.x = a;
-        v.y = b;
-        return v;
-    }
-    __device__ static void stp(double* p, P v) { *(v2d JC_GLOBAL*)(p) = v; }
-    __device__ static void stpn(double* p, P v) { __builtin_nontemporal_store(v, (v2d JC_GLOBAL*)(p)); }
-    __device__ static void st1a(double* p, P v) { *(double JC_GLOBAL*)(p) = v.x; }
-    __device__ static void st1b(double* p, P v) { *(double JC_GLOBAL*)(p) = v.y; }
-};
-
-template <> struct Tr<float> {
-    using C = float;
-    __device__ static void ld(const float* p, float& a, float& b)
-    {
-        const v2f v = *(const v2f JC_GLOBAL*)(p);
-        a = v.x;
-        b = v.y;
-    }
-    __device__ static void st(float* p, float a, float b)
-    {
-        v2f v;
-        v.x = a;
-        v.y = b;
-        *(v2f JC_GLOBAL*)(p) = v;
-    }
-    __device__ static void st1(float* p, float a) { *(float JC_GLOBAL*)(p) = a; }
-    __device__ static void stn(float* p, float a, float b)
-    {
-        v2f v;
-        v.x = a;
-        v.y = b;
-        __builtin_nontemporal_store(v, (v2f JC_GLOBAL*)(p));
-    }
-    using P = v2f;
-    __device__ static P pack(float a, float b)
-    {
-        v2f v;
-        v.x = a;
-        v.y = b;
-        return v;
-    }
-    __device__ static void stp(float* p, P v) { *(v2f JC_GLOBAL*)(p) = v; }
-    __device__ static void stpn(float* p, P v) { __builtin_nontemporal_store(v, (v2f JC_GLOBAL*)(p)); }
-    __device__ static void st1a(float* p, P v) { *(float JC_GLOBAL*)(p) = v.x; }
-    __device__ static void st1b(float* p, P v) { *(float JC_GLOBAL*)(p) = v.y; }
-};
-
-template <> struct Tr<bf16> {
-    using C = float;
-    __device__ static void ld(const bf16* p, float& a, float& b)
-    {
-        const uint32_t w = *(const uint32_t JC_GLOBAL*)(p);    // x at the lower address
-        a = bf16_to_f32(w & 0xffffu);
-        b = bf16_to_f32(w >> 16);
-    }
-    __device__ static void st(bf16* p, float a, float b)
-    {
-        *(uint32_t JC_GLOBAL*)(p) = f32_to_bf16(a) | (f32_to_bf16(b) << 16);
-    }
-    __device__ static void st1(bf16* p, float a) { *(uint16_t JC_GLOBAL*)(p) = (uint16_t)f32_to_bf16(a); }
-    __device__ static void stn(bf16* p, float a, float b)
-    {
-        __builtin_nontemporal_store(f32_to_bf16(a) | (f32_to_bf16(b) << 16), (uint32_t JC_GLOBAL*)(p));
-    }
-    using P = uint32_t;                           // x in the low half
-    __device__ static P pack(float a, float b) { return f32_to_bf16(a) | (f32_to_bf16(b) << 16); }
-    __device__ static void stp(bf16* p, P v) { *(uint32_t JC_GLOBAL*)(p) = v; }
-    __device__ static void stpn(bf16* p, P v) { __builtin_nontemporal_store(v, (uint32_t JC_GLOBAL*)(p)); }
-    __device__ static void st1a(bf16* p, P v) { *(uint16_t JC_GLOBAL*)(p) = (uint16_t)(v & 0xffffu); }
-    __device__ static void st1b(bf16* p, P v) { *(uint16_t JC_GLOBAL*)(p) = (uint16_t)(v >> 16); }
-};
-
 // Which arrays of a block a sweep works on: the iterate u (with source b)
 // or the refinement correction d (with source r_lo).
 enum { FIELD_U = 0, FIELD_D = 1 };
@@ -1451,104 +1318,6 @@ k_resident(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items,
 }
 // ---- resident sweeps: end ----
 
-// First inner sweep of a refinement step: d_1 = lo((0 + r_lo) / 6)
-// (d_0 = 0, so no neighbour is read); writes copy 1 of d and its faces.
-template <typename T>
-__global__ void __launch_bounds__(256)
-k_ir_first(const BlockDesc* __restrict__ blocks)
-{
-    using C = typename Tr<T>::C;
-    const BlockDesc* B = blocks + blockIdx.y;
-    const int nx = B->n[0], ny = B->n[1], nz = B->n[2];
-    const int64_t lp = B->lpitch, ll = B->lplane;
-    const int64_t ldx = face_ld(ny), ldy = face_ld(nx);
-    const T* rl = static_cast<const T*>(B->rlo);
-    T* d = static_cast<T*>(B->d[1]);
-    const int npair = (nx + 1) / 2;
-    const int64_t rows = (int64_t)ny * nz;
-    for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
-        const int y = (int)(r % ny) + 1;
-        const int z = (int)(r / ny) + 1;
-        for (int k = threadIdx.x; k < npair; k += 256) {
-            const int xa = 2 * k + 1;
-            const bool b_ok = xa + 1 <= nx;
-            const int64_t at = (int64_t)z * ll + (int64_t)y * lp + xa;
-            C sa, sb;
-            Tr<T>::ld(rl + at, sa, sb);
-            const C zero = C(0);
-            const C va = div6(zero + sa);
-            const C vb = div6(zero + sb);
-            C ga, gb;
-            Tr<T>::ld(static_cast<const T*>(B->d[1]) + at, ga, gb);   // keeps the x = nx + 1 ghost
-            Tr<T>::st(d + at, va, b_ok ? vb : gb);
-            T* oxm = static_cast<T*>(B->lgout[XM][1]);
-            T* oxp = static_cast<T*>(B->lgout[XP][1]);
-            T* oym = static_cast<T*>(B->lgout[YM][1]);
-            T* oyp = static_cast<T*>(B->lgout[YP][1]);
-            T* ozm = static_cast<T*>(B->lgout[ZM][1]);
-            T* ozp = static_cast<T*>(B->lgout[ZP][1]);
-            const int64_t xfi = (int64_t)(z - 1) * ldx + (y - 1);
-            const int64_t yfi = (int64_t)(z - 1) * ldy + (xa - 1);
-            const int64_t zfi = (int64_t)(y - 1) * ldy + (xa - 1);
-            if (xa == 1 && oxm) Tr<T>::st1(oxm + xfi, va);
-            if (xa == nx && oxp) Tr<T>::st1(oxp + xfi, va);
-            if (b_ok && xa + 1 == nx && oxp) Tr<T>::st1(oxp + xfi, vb);
-            if (y == 1 && oym) Tr<T>::st(oym + yfi, va, vb);
-            if (y == ny && oyp) Tr<T>::st(oyp + yfi, va, vb);
-            if (z == 1 && ozm) Tr<T>::st(ozm + zfi, va, vb);
-            if (z == nz && ozp) Tr<T>::st(ozp + zfi, va, vb);
-        }
-    }
-}
-
-// Outer update of the refinement: u(copy p) += (double) d(copy q) on the
-// interior; the updated face cells go to the u face buffers of slot p.
-template <typename T>
-__global__ void __launch_bounds__(256)
-k_ir_update(const BlockDesc* __restrict__ blocks, int p, int q)
-{
-    using C = typename Tr<T>::C;
-    const BlockDesc* B = blocks + blockIdx.y;
-    const int nx = B->n[0], ny = B->n[1], nz = B->n[2];
-    const int64_t ldx = face_ld(ny), ldy = face_ld(nx);
-    double* u = B->u[p];
-    const T* d = static_cast<const T*>(B->d[q]);
-    const int npair = (nx + 1) / 2;
-    const int64_t rows = (int64_t)ny * nz;
-    for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
-        const int y = (int)(r % ny) + 1;
-        const int z = (int)(r / ny) + 1;
-        for (int k = threadIdx.x; k < npair; k += 256) {
-            const int xa = 2 * k + 1;
-            const bool b_ok = xa + 1 <= nx;
-            double* up = u + (int64_t)z * B->plane + (int64_t)y * B->pitch + xa;
-            double ua, ub;
-            Tr<double>::ld(up, ua, ub);
-            C da, db;
-            Tr<T>::ld(d + (int64_t)z * B->lplane + (int64_t)y * B->lpitch + xa, da, db);
-            const double va = ua + (double)da;
-            const double vb = b_ok ? ub + (double)db : ub;
-            Tr<double>::st(up, va, vb);
-            double* oxm = B->gout[XM][p];
-            double* oxp = B->gout[XP][p];
-            double* oym = B->gout[YM][p];
-            double* oyp = B->gout[YP][p];
-            double* ozm = B->gout[ZM][p];
-            double* ozp = B->gout[ZP][p];
-            const int64_t xfi = (int64_t)(z - 1) * ldx + (y - 1);
-            const int64_t yfi = (int64_t)(z - 1) * ldy + (xa - 1);
-            const int64_t zfi = (int64_t)(y - 1) * ldy + (xa - 1);
-            if (xa == 1 && oxm) Tr<double>::st1(oxm + xfi, va);
-            if (xa == nx && oxp) Tr<double>::st1(oxp + xfi, va);
-            if (b_ok && xa + 1 == nx && oxp) Tr<double>::st1(oxp + xfi, vb);
-            if (y == 1 && oym) Tr<double>::st(oym + yfi, va, vb);
-            if (y == ny && oyp) Tr<double>::st(oyp + yfi, va, vb);
-            if (z == 1 && ozm) Tr<double>::st(ozm + zfi, va, vb);
-            if (z == nz && ozp) Tr<double>::st(ozp + zfi, va, vb);
-        }
-    }
-}
-
 // Zero `words` 8-byte words at p (grid-stride).
 __global__ void __launch_bounds__(256)
 k_zero(uint64_t* __restrict__ p, int64_t words)
@@ -1576,132 +1345,6 @@ k_reduce(const double* __restrict__ partials, const int32_t* __restrict__ ranges
     __syncthreads();
     if (threadIdx.x == 0)
         out[m] = ((w[0] + w[1]) + w[2]) + w[3];
-}
-
-// Address of the cell (slow, fast) of the plane of face f, at depth
-// `ghost` (0: the outermost interior plane, 1: the ghost plane beyond it).
-__device__ __forceinline__ int64_t face_cell(const BlockDesc& B, int f, int slow, int fast, int ghost)
-{
-    const int nx = B.n[0], ny = B.n[1], nz = B.n[2];
-    int x, y, z;
-    switch (f) {
-    case XM: x = ghost ? 0 : 1;            y = fast + 1; z = slow + 1; break;
-    case XP: x = ghost ? nx + 1 : nx;      y = fast + 1; z = slow + 1; break;
-    case YM: y = ghost ? 0 : 1;            x = fast + 1; z = slow + 1; break;
-    case YP: y = ghost ? ny + 1 : ny;      x = fast + 1; z = slow + 1; break;
-    case ZM: z = ghost ? 0 : 1;            x = fast + 1; y = slow + 1; break;
-    default: z = ghost ? nz + 1 : nz;      x = fast + 1; y = slow + 1; break;
-    }
-    return (int64_t)z * B.plane + (int64_t)y * B.pitch + x;
-}
-
-__global__ void __launch_bounds__(256)
-k_pack(const BlockDesc* __restrict__ blocks, const PairDesc* __restrict__ pairs, int parity, int slot)
-{
-    const PairDesc& P = pairs[blockIdx.z];
-    const int slow = blockIdx.y;
-    const int fast = blockIdx.x * 256 + threadIdx.x;
-    if (slow >= P.slow || fast >= P.fast)
-        return;
-    const BlockDesc& B = blocks[P.src_block];
-    P.buf[slot][(int64_t)slow * face_ld(P.fast) + fast] = B.u[parity][face_cell(B, P.src_face, slow, fast, 0)];
-}
-
-__global__ void __launch_bounds__(256)
-k_unpack(const BlockDesc* __restrict__ blocks, const PairDesc* __restrict__ pairs, int parity)
-{
-    const PairDesc& P = pairs[blockIdx.z];
-    const int slow = blockIdx.y;
-    const int fast = blockIdx.x * 256 + threadIdx.x;
-    if (slow >= P.slow || fast >= P.fast)
-        return;
-    const BlockDesc& B = blocks[P.dst_block];
-    B.u[parity][face_cell(B, P.dst_face, slow, fast, 1)] = P.buf[1][(int64_t)slow * face_ld(P.fast) + fast];
-}
-
-// The pairing's transfer: every send buffer into the receive buffer
-// pre-posted for it.  Buffers are 256-byte aligned with an even number of
-// elements: 16-byte vectors.
-__global__ void __launch_bounds__(256)
-k_exchange(const PairDesc* __restrict__ pairs)
-{
-    const PairDesc& P = pairs[blockIdx.y];
-    const int64_t n2 = P.span >> 1;
-    const double2* __restrict__ a = reinterpret_cast<const double2*>(P.buf[0]);
-    double2* __restrict__ b = reinterpret_cast<double2*>(P.buf[1]);
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n2; i += (int64_t)gridDim.x * 256)
-        b[i] = a[i];
-}
-
-// Rows of every block's padded array: blockIdx.y = block; the work-group
-// walks rows (z, y) with a stride, lanes cover x in [0, nx+1].
-__global__ void __launch_bounds__(256)
-k_scatter(const BlockDesc* __restrict__ blocks, const double* __restrict__ g, int64_t gnx,
-          int64_t gny, int which)
-{
-    const BlockDesc& B = blocks[blockIdx.y];
-    const int nx = B.n[0], ny = B.n[1], nz = B.n[2];
-    const int64_t gpitch = gnx + 2, gplane = (gnx + 2) * (gny + 2);
-    const int64_t rows = (int64_t)(ny + 2) * (nz + 2);
-    for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
-        const int y = (int)(r % (ny + 2));
-        const int z = (int)(r / (ny + 2));
-        const int64_t grow = (int64_t)(B.off[2] + z) * gplane + (int64_t)(B.off[1] + y) * gpitch + B.off[0];
-        const int64_t brow = (int64_t)z * B.plane + (int64_t)y * B.pitch;
-        const bool col_row = y >= 1 && y <= ny && z >= 1 && z <= nz;
-        const int64_t col_at = (int64_t)(z - 1) * face_ld(ny) + (y - 1);
-        for (int x = threadIdx.x; x < nx + 2; x += 256) {
-            const double v = g[grow + x];
-            if (which == 0) {
-                B.u[0][brow + x] = v;
-                B.u[1][brow + x] = v;
-                // the compact Dirichlet ghost columns of unpaired x faces
-                if (col_row && x == 0 && B.xg[XM])
-                    const_cast<double*>(B.xg[XM])[col_at] = v;
-                if (col_row && x == nx + 1 && B.xg[XP])
-                    const_cast<double*>(B.xg[XP])[col_at] = v;
-            } else {
-                const_cast<double*>(B.b)[brow + x] = v;
-            }
-        }
-    }
-}
-
-// Interior cells, plus the cells on the global Dirichlet shell.
-__global__ void __launch_bounds__(256)
-k_gather(const BlockDesc* __restrict__ blocks, double* __restrict__ g, int64_t gnx, int64_t gny,
-         int64_t gnz, int which, int parity)
-{
-    const BlockDesc& B = blocks[blockIdx.y];
-    const int nx = B.n[0], ny = B.n[1], nz = B.n[2];
-    const int64_t gpitch = gnx + 2, gplane = (gnx + 2) * (gny + 2);
-    const int64_t rows = (int64_t)(ny + 2) * (nz + 2);
-    const double* src = which == 0 ? B.u[parity] : B.b;
-    for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
-        const int y = (int)(r % (ny + 2));
-        const int z = (int)(r / (ny + 2));
-        const int64_t gy = B.off[1] + y, gz = B.off[2] + z;
-        const bool rowin = (y >= 1 && y <= ny && z >= 1 && z <= nz);
-        const bool rowshell = (gy == 0 || gy == gny + 1 || gz == 0 || gz == gnz + 1);
-        const int64_t grow = gz * gplane + gy * gpitch + B.off[0];
-        const int64_t brow = (int64_t)z * B.plane + (int64_t)y * B.pitch;
-        for (int x = threadIdx.x; x < nx + 2; x += 256) {
-            const int64_t gx = B.off[0] + x;
-            const bool in = rowin && x >= 1 && x <= nx;
-            const bool shell = rowshell || gx == 0 || gx == gnx + 1;
-            if (in || shell)
-                g[grow + x] = src[brow + x];
-        }
-    }
-}
-
-// Row kernels: one work-group per row of the largest block, up to 16384.
-dim3 row_grid(int nblocks, int64_t max_rows)
-{
-    int64_t per = max_rows;
-    if (per > 16384) per = 16384;
-    if (per < 1) per = 1;
-    return dim3((unsigned)per, (unsigned)nblocks);
 }
 
 }  // namespace
@@ -1944,35 +1587,6 @@ hipError_t launch_ir_inner(const BlockDesc* blocks, const Item* items, int nitem
     }
 }
 
-hipError_t launch_ir_first(const BlockDesc* blocks, int nblocks, int64_t max_rows, int lo_dtype, hipStream_t s)
-{
-    if (nblocks <= 0)
-        return hipSuccess;
-    const dim3 grid = row_grid(nblocks, max_rows);
-    switch (lo_dtype) {
-    case 0: hipLaunchKernelGGL(k_ir_first<double>, grid, dim3(256), 0, s, blocks); break;
-    case 1: hipLaunchKernelGGL(k_ir_first<float>, grid, dim3(256), 0, s, blocks); break;
-    case 2: hipLaunchKernelGGL(k_ir_first<bf16>, grid, dim3(256), 0, s, blocks); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_ir_update(const BlockDesc* blocks, int nblocks, int64_t max_rows, int p, int q, int lo_dtype,
-                            hipStream_t s)
-{
-    if (nblocks <= 0)
-        return hipSuccess;
-    const dim3 grid = row_grid(nblocks, max_rows);
-    switch (lo_dtype) {
-    case 0: hipLaunchKernelGGL(k_ir_update<double>, grid, dim3(256), 0, s, blocks, p, q); break;
-    case 1: hipLaunchKernelGGL(k_ir_update<float>, grid, dim3(256), 0, s, blocks, p, q); break;
-    case 2: hipLaunchKernelGGL(k_ir_update<bf16>, grid, dim3(256), 0, s, blocks, p, q); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s)
 {
     const int64_t words = (int64_t)(bytes / 8);
@@ -1990,56 +1604,6 @@ hipError_t launch_reduce(const double* partials, const int32_t* ranges, int nmem
     if (nmembers <= 0)
         return hipSuccess;
     hipLaunchKernelGGL(k_reduce, dim3(nmembers), dim3(256), 0, s, partials, ranges, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_pack(const BlockDesc* blocks, const PairDesc* pairs, int npairs, int max_slow,
-                       int max_fast, int parity, int slot, hipStream_t s)
-{
-    if (npairs <= 0)
-        return hipSuccess;
-    const dim3 grid((max_fast + 255) / 256, max_slow, npairs);
-    hipLaunchKernelGGL(k_pack, grid, dim3(256), 0, s, blocks, pairs, parity, slot);
-    return hipGetLastError();
-}
-
-hipError_t launch_exchange(const PairDesc* pairs, int npairs, int64_t max_count, hipStream_t s)
-{
-    if (npairs <= 0)
-        return hipSuccess;
-    int64_t chunks = (max_count / 2 + 255) / 256;
-    if (chunks < 1) chunks = 1;
-    if (chunks > 1024) chunks = 1024;
-    hipLaunchKernelGGL(k_exchange, dim3((unsigned)chunks, npairs), dim3(256), 0, s, pairs);
-    return hipGetLastError();
-}
-
-hipError_t launch_unpack(const BlockDesc* blocks, const PairDesc* pairs, int npairs, int max_slow,
-                         int max_fast, int parity, hipStream_t s)
-{
-    if (npairs <= 0)
-        return hipSuccess;
-    const dim3 grid((max_fast + 255) / 256, max_slow, npairs);
-    hipLaunchKernelGGL(k_unpack, grid, dim3(256), 0, s, blocks, pairs, parity);
-    return hipGetLastError();
-}
-
-hipError_t launch_scatter(const BlockDesc* blocks, int nblocks, int64_t max_rows, const double* global,
-                          int64_t gnx, int64_t gny, int which, hipStream_t s)
-{
-    if (nblocks <= 0)
-        return hipSuccess;
-    hipLaunchKernelGGL(k_scatter, row_grid(nblocks, max_rows), dim3(256), 0, s, blocks, global, gnx, gny, which);
-    return hipGetLastError();
-}
-
-hipError_t launch_gather(const BlockDesc* blocks, int nblocks, int64_t max_rows, double* global, int64_t gnx,
-                         int64_t gny, int64_t gnz, int which, int parity, hipStream_t s)
-{
-    if (nblocks <= 0)
-        return hipSuccess;
-    hipLaunchKernelGGL(k_gather, row_grid(nblocks, max_rows), dim3(256), 0, s, blocks, global, gnx, gny, gnz,
-                       which, parity);
     return hipGetLastError();
 }
 

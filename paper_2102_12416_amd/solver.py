@@ -128,7 +128,8 @@ class Solver:
 
     def store(self, which=L.JC_FIELD_U) -> torch.Tensor:
         """Current iterate (or the source) as a global padded device tensor."""
-        out = torch.zeros(self.padded_shape(), dtype=torch.float64, device=self.device)
+        # every element is written (interior and Dirichlet shell)
+        out = torch.empty(self.padded_shape(), dtype=torch.float64, device=self.device)
         self.stream.wait_stream(torch.cuda.current_stream(self.device))
         check(L.lib.jc_store_field(self._ctx, which, ctypes.c_void_p(out.data_ptr())))
         out.record_stream(self.stream)
