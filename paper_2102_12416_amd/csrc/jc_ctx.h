@@ -90,6 +90,7 @@ inline bool tile_shape_ok(int tile_x, int tile_y, bool narrow = false)
     return ok_x && ok_y && threads >= 64 && threads <= 1024 && (!narrow || tile_x <= kNarrowTileMax);
 }
 constexpr int kMinZChunk = 16;
+constexpr int kComputeUnits = 256;                // of an MI355X
 // largest pace (ticks of the 100 MHz clock per plane step): each wait of a
 // work-group is bounded by 4096 sleeps of 64 cycles, about 100 us
 constexpr int64_t kMaxPace = 10000;
@@ -134,6 +135,7 @@ struct jc_ctx {
     // (t2_zc 0: the one-sweep z_chunk, at least kTwoStepMinZ)
     int t2_rows = jc_rt::kTwoStepRows;
     int t2_zc = 0;
+    bool t2_auto = false;           // t2_zc is default_multi_planes'
     // pace of the one-sweep launches of the solve loop (jc_set_pace): ticks
     // of the 100 MHz constant clock per plane step; 0 = none
     uint32_t pace = 0;

@@ -62,11 +62,12 @@ int64_t idle_cells(const jc_ctx* c, int tx)
     return idle;
 }
 
-// Default tile: 64 cells wide unless 32 leaves fewer idle lanes by more
-// than 1/16 of the cells; 8 rows; z chunks halved from the full depth
-// until the launch has at least 4096 tiles (16 per compute unit) or
-// chunks reach 16.
-void default_tiles(const jc_ctx* c, int* tx, int* ty, int* zc)
+// The tile of a context that was given part of one, and the size of every
+// context's work-list region: 64 cells wide unless 32 leaves fewer idle
+// lanes by more than 1/16 of the cells; 8 rows; z chunks halved from the
+// full depth until the launch has at least 4096 tiles (16 per compute unit)
+// or chunks reach 16.
+void region_tiles(const jc_ctx* c, int* tx, int* ty, int* zc)
 {
     int64_t maxz = 1, cells = 0;
     for (const HostBlock& b : c->blocks) {
@@ -85,6 +86,105 @@ void default_tiles(const jc_ctx* c, int* tx, int* ty, int* zc)
     *tx = x;
     *ty = t;
     *zc = z;
+}
+
+// Default tile of a context that was given none; at most max_items tiles.
+//
+// Width 64, or 32 where that idles fewer lanes by more than 0.18 of the cells
+// (bfloat16, whose 64 cells are one line: 0.4; 420 x 401 x 390 in uneven
+// blocks, 0.13: 32 cells 321 us, 64 cells 241) and for rows of at most 32.
+//
+// Rows and planes, by what bounds a launch:
+//  - A small grid (up to 2^20 cells) is bound by the latency of its chain of
+//    plane steps: as many z chunks as keep one work-group of 8 waves per
+//    compute unit, down to 2 planes (64^3: 16 rows x 2 planes 3.4 us, 8 x 16
+//    7.2; 100 x 90 x 80: 16 x 4 4.8 us, 8 x 10 6.0).
+//  - One block, or equal blocks with long columns: one round of work-groups
+//    on the compute units with 8 waves each (two of 16 for ragged shapes),
+//    and the longest columns that allows: few halo planes, and neighbours
+//    march together, so shared halo rows hit in L2 (256^3: 16 x 64 50 us,
+//    8 x 16 64; 512^3: 16 x 512 368 us, 8 x 64 433).  Taken where at most 15 %
+//    of the round idles (several blocks: 5 %); bfloat16 is bound by issue and
+//    gains nothing.
+//  - Otherwise many rounds of short work-groups, 8 rows by at most 12 planes
+//    (bfloat16: 16), whose tail is short (the uneven blocks above: 8 x 63
+//    planes 321 us with 32 cells, 247 with 32 x 8 x 11).
+//  Between these -- up to the size where a round's columns reach 12 planes,
+//  and where many rounds are left up to 2^24 cells -- nothing beats the
+//  region's own tile by more than its spread.
+void default_tiles(const jc_ctx* c, int64_t max_items, int* tx, int* ty, int* zc)
+{
+    int64_t maxz = 1, maxx = 1, cells = 0;
+    bool equal = true;
+    const HostBlock& b0 = c->blocks[0];
+    for (const HostBlock& b : c->blocks) {
+        maxz = std::max(maxz, b.n[2]);
+        maxx = std::max(maxx, b.n[0]);
+        cells += b.n[0] * b.n[1] * b.n[2];
+        equal = equal && b.n[0] == b0.n[0] && b.n[1] == b0.n[1] && b.n[2] == b0.n[2];
+    }
+    maxz = std::min<int64_t>(maxz, 1 << 20);
+    const bool bf = c->opt.ir_enable && c->opt.ir_dtype == JC_BF16;
+    const bool narrow = (idle_cells(c, 64) - idle_cells(c, 32)) * 100 > cells * (bf ? 40 : 18) || maxx <= 32;
+    const int x = narrow ? 32 : 64;
+    const bool small = cells <= ((int64_t)1 << 20);
+    // one round: rows, and work-groups per compute unit
+    struct Shape {
+        int rows, per_cu;
+    };
+    static const Shape wide_shapes[] = {{16, 1}, {8, 2}, {4, 4}, {4, 3}, {32, 2}};
+    static const Shape narrow_shapes[] = {{32, 1}, {16, 2}, {8, 4}, {8, 3}};
+    const Shape* shapes = narrow ? narrow_shapes : wide_shapes;
+    const int nshapes = narrow ? 4 : 5;
+    double best = 0, balance = 0;
+    int rows = 0, planes = 0;
+    for (int i = 0; i < nshapes; ++i) {
+        const int64_t cap = (int64_t)kComputeUnits * shapes[i].per_cu;
+        const bool long_only = i >= 2;            // 2- and 16-wave work-groups: for long columns
+        int pick = 0;
+        for (int64_t k = 1; k <= maxz; ++k) {
+            const int64_t z = (maxz + k - 1) / k;
+            if (z < (long_only ? kMinZChunk : 2))
+                break;
+            const int64_t n = items_for(c, x, shapes[i].rows, (int)z);
+            if (n > cap)
+                break;
+            if (n <= max_items)
+                pick = (int)z;
+        }
+        if (!pick)
+            continue;
+        const int64_t steps = items_for(c, x, shapes[i].rows, 1);   // plane steps of all tiles
+        const double used = (double)steps / ((double)cap * pick);
+        const double score = used * pick / (pick + 2.0);
+        if (score > best * 1.08) {
+            best = score;
+            balance = used;
+            rows = shapes[i].rows;
+            planes = pick;
+        }
+    }
+    *tx = x;
+    if (rows && planes < 12 && small) {
+        *ty = rows;
+        *zc = planes;
+        return;
+    }
+    const bool round = rows && planes >= 12 && !bf &&
+                       (c->nb() == 1 ? balance >= 0.85 : equal && planes >= 64 && balance >= 0.95);
+    if (round) {
+        *ty = rows;
+        *zc = planes;
+        return;
+    }
+    if ((rows && planes < 12) || cells <= (int64_t)1 << 24)
+        return region_tiles(c, tx, ty, zc);
+    const int64_t most = bf ? 16 : 12;
+    int64_t z = (maxz + (maxz + most - 1) / most - 1) / ((maxz + most - 1) / most);
+    while (items_for(c, x, 8, (int)z) > max_items)
+        ++z;
+    *ty = 8;
+    *zc = (int)z;
 }
 
 void build_items(jc_ctx* c)
@@ -123,6 +223,40 @@ void build_items(jc_ctx* c)
         const auto mid = std::stable_partition(c->items.begin(), c->items.end(), boundary);
         c->n_bnd = mid - c->items.begin();
     }
+}
+
+// Default planes of the multi-sweep launch (temporal blocking; 16 rows).  A
+// work-group marches up a column of zc planes in zc + 2 (depth - 1) steps
+// after a prologue of about two; a launch takes as many rounds of work-groups
+// as the compute units divide them into, and costs rounds x steps.  Several
+// rounds cost 15 % more, since their work-groups drift apart in z and miss L2
+// on the halo rows they share.  A small grid gets columns of a plane or two,
+// a large one whole rounds of long columns.  Measured, three sweeps per launch
+// (before: 8 planes, or 32 and the one-sweep chunk on large grids): 64^3
+// 16 x 1 7.3 us a launch against 11.4, 200 x 180 x 160 16 x 32 32 against 47,
+// 256^3 16 x 64 61 against 83, 512^3 16 x 512 423 against 443, and jc_autotune's
+// own shapes at 512^3 and 512 x 768 x 1536.
+int default_multi_planes(const jc_ctx* c)
+{
+    const HostBlock& b = c->blocks[0];
+    const int64_t nz = std::min<int64_t>(b.n[2], 1 << 20);
+    const int64_t tiles = (b.n[0] + 63) / 64 * ((b.n[1] + kTwoStepRows - 1) / kTwoStepRows);
+    double best = 0;
+    int64_t planes = nz;
+    for (int64_t k = 1; k <= nz; ++k) {
+        const int64_t zc = (nz + k - 1) / k;
+        const int64_t n = tiles * ((nz + zc - 1) / zc);
+        // short columns only while they are needed to fill one round
+        if (k > 1 && zc < kMinZChunk && n > kComputeUnits)
+            break;
+        const int64_t rounds = (n + kComputeUnits - 1) / kComputeUnits;
+        const double cost = (double)rounds * (double)(zc + 2 * c->depth()) * (rounds > 1 ? 1.15 : 1.0);
+        if (best == 0 || cost < best) {
+            best = cost;
+            planes = zc;
+        }
+    }
+    return (int)planes;
 }
 
 int validate_options(const jc_options* opt)
@@ -260,11 +394,17 @@ int build_geometry(jc_ctx* c, const int64_t grid[3], const std::vector<int64_t> 
     if (c->opt.resident && (c->nb() != 1 || !jc::resident_fits(c->blocks[0].n[0], c->blocks[0].n[1], c->blocks[0].n[2])))
         return fail(JC_ERR_INVALID, "options.resident needs a context of one block of at most 32 planes with "
                                     "(nx + 1) / 2 * ny <= 512 cell pairs and an LDS need within 64 KiB");
-    default_tiles(c, &c->tile_x, &c->tile_y, &c->z_chunk);
-    build_items(c);
     // the work-list region is sized for the finest tiling the tuner may pick
-    c->max_items = std::max<int64_t>({(int64_t)c->items.size(), items_for(c, 32, 4, kMinZChunk),
+    region_tiles(c, &c->tile_x, &c->tile_y, &c->z_chunk);
+    c->max_items = std::max<int64_t>({items_for(c, c->tile_x, c->tile_y, c->z_chunk), items_for(c, 32, 4, kMinZChunk),
                                       items_for(c, 16, 8, kMinZChunk)});
+    // boundary-first iterations need tiles away from the faces: as before
+    if (c->opt.tile_x <= 0 && c->opt.tile_y <= 0 && c->opt.z_chunk <= 0 && !c->opt.overlap)
+        default_tiles(c, c->max_items, &c->tile_x, &c->tile_y, &c->z_chunk);
+    build_items(c);
+    c->t2_auto = c->opt.temporal && c->opt.z_chunk <= 0;
+    if (c->t2_auto)
+        c->t2_zc = default_multi_planes(c);
     if (c->max_items > (int64_t)1 << 30)
         return fail(JC_ERR_INVALID, "work list too long");
     // arena layout
@@ -527,8 +667,8 @@ int do_sweep(jc_ctx* c, bool fused, bool resid)
     return JC_OK;
 }
 
-// Planes per two-sweep work-group: the shape set or tuned, else the
-// one-sweep z_chunk (at least kTwoStepMinZ), halved down to
+// Planes per multi-sweep work-group: the default, set or tuned shape, else
+// (a z_chunk was given) the one-sweep z_chunk (at least kTwoStepMinZ), halved down to
 // kTwoStepFloorZ while the launch would have fewer than
 // kTwoStepMinGroups work-groups (a small grid alone).
 int two_step_chunk(const jc_ctx* c)
@@ -977,6 +1117,7 @@ int tune_two_step(jc_ctx* c, int reps)
     const Cand best = *std::min_element(cand.begin(), cand.end(), [](const Cand& a, const Cand& b) { return a.ms < b.ms; });
     c->t2_rows = best.rows;
     c->t2_zc = best.zc;
+    c->t2_auto = false;
     c->pace = 0;
     free_graphs(c);
     return JC_OK;
@@ -1579,6 +1720,10 @@ int jc_set_tiles(jc_ctx* c, int tile_x, int tile_y, int z_chunk)
     c->tile_y = tile_y;
     c->z_chunk = z_chunk;
     c->pace = 0;                           // a pace belongs to a shape
+    if (c->t2_auto) {                      // the multi-sweep launch follows a z_chunk that was set
+        c->t2_auto = false;
+        c->t2_zc = 0;
+    }
     build_items(c);
     c->hranges[1] = (int32_t)c->items.size();
     free_graphs(c);                        // graphs hold the old launch shapes
@@ -1604,6 +1749,7 @@ int jc_set_temporal_tiles(jc_ctx* c, int rows, int z_chunk)
         return fail(JC_ERR_INVALID, "z_chunk must be >= 1");
     c->t2_rows = rows;
     c->t2_zc = z_chunk;
+    c->t2_auto = false;
     c->pace = 0;                           // a pace belongs to a shape
     free_graphs(c);                        // graphs hold the old launch shapes
     return JC_OK;
