@@ -235,7 +235,8 @@ int jc_unpack_faces(jc_ctx* ctx);
 int jc_sweep(jc_ctx* ctx);
 
 /* n full iterations.  Staged mode: n x (pack, exchange, unpack, sweep);
- * fused mode: n single launches.  Graph-captured when use_graphs is set
+ * fused mode: n single launches.  Captured as a graph when use_graphs is set,
+ * the window has 8 launches or more
  * and the stream is not the null stream. */
 int jc_iterate(jc_ctx* ctx, int64_t n);
 

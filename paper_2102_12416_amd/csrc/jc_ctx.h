@@ -91,6 +91,11 @@ inline bool tile_shape_ok(int tile_x, int tile_y, bool narrow = false)
 }
 constexpr int kMinZChunk = 16;
 constexpr int kComputeUnits = 256;                // of an MI355X
+// A graph replay costs about 20 us whatever it holds and its capture some 8 us
+// a launch once, an eager launch 2.4 us up to the eighth in a row (then 3 to 4):
+// windows of fewer launches than this run eagerly (64^3, six launches alone:
+// 32 us eager, 38 as a graph; nine: 48 and 48).
+constexpr int64_t kGraphMinLaunches = 8;
 // largest pace (ticks of the 100 MHz clock per plane step): each wait of a
 // work-group is bounded by 4096 sleeps of 64 cycles, about 100 us
 constexpr int64_t kMaxPace = 10000;
@@ -165,7 +170,8 @@ struct jc_ctx {
     std::vector<BlockDesc> hdesc;
     std::vector<PairDesc> hpairs;
     int32_t hranges[2] = {0, 0};
-    double* h_result = nullptr;     // pinned
+    jc::HostSum* h_result = nullptr;   // pinned: the residual sum of the last check
+    uint64_t check_seq = 0;            // its sequence number
     // host-staged exchange: pinned send and receive halves, per-pair offsets
     char* h_stage = nullptr;
     size_t h_stage_bytes = 0;
@@ -200,7 +206,6 @@ struct jc_ctx {
     Item* d_items() const { return reinterpret_cast<Item*>(arena + off_items); }
     double* d_partials() const { return reinterpret_cast<double*>(arena + off_partials); }
     int32_t* d_ranges() const { return reinterpret_cast<int32_t*>(arena + off_ranges); }
-    double* d_result() const { return reinterpret_cast<double*>(arena + off_result); }
     int nb() const { return (int)blocks.size(); }
     int64_t max_rows() const
     {
@@ -229,6 +234,9 @@ inline bool narrow_storage(const jc_ctx* c) { return c->opt.ir_enable && c->opt.
 hipEvent_t take_event(jc_ctx* c);
 int drain_timing(jc_ctx* c);
 int check_ready(jc_ctx* c);
+// Waits until the sums host[0 .. n) of check `seq`, the last work enqueued on
+// the stream, have arrived.
+hipError_t wait_sums(hipStream_t s, const jc::HostSum* host, int n, uint64_t seq);
 int do_pack(jc_ctx* c, int slot);
 
 // Runs `launch` on the context's stream, bracketed by timing events of

@@ -73,7 +73,8 @@ struct jc_group {
            footprint = 0;
     char* scratch = nullptr;
     bool bound = false;
-    double* h_out = nullptr;            // pinned, one per member (or h_out_plain)
+    jc::HostSum* h_out = nullptr;       // pinned, one per member; null with the static-scratch binding
+    uint64_t check_seq = 0;
     std::vector<double> h_out_plain;    // pageable, one per member: the static-scratch binding
     int static_dev = -1;                // device whose static scratch the group holds (-1: none)
     int parity = 0;                     // launch parity; items hold member flips
@@ -449,7 +450,6 @@ int bind_common(jc_group* g, char* scratch, bool plain)
     g->scratch = scratch;
     int st = JC_OK;
     if (plain) {
-        g->h_out = g->h_out_plain.data();
         for (jc_ctx* c : g->members)
             if (c->stream != g->stream && st == JC_OK)
                 st = ghip(hipStreamSynchronize(c->stream), "hipStreamSynchronize");
@@ -458,8 +458,10 @@ int bind_common(jc_group* g, char* scratch, bool plain)
         if (st == JC_OK)
             st = ghip(jc::launch_zero(scratch, g->footprint, g->stream), "clear scratch");
     } else {
-        st = ghip(hipHostMalloc(reinterpret_cast<void**>(&g->h_out), sizeof(double) * g->members.size(),
+        st = ghip(hipHostMalloc(reinterpret_cast<void**>(&g->h_out), sizeof(jc::HostSum) * g->members.size(),
                                 hipHostMallocDefault), "hipHostMalloc");
+        if (st == JC_OK)
+            std::fill_n(g->h_out, g->members.size(), jc::HostSum{0.0, 0});
         // order the group stream after every member's queued work
         for (jc_ctx* c : g->members) {
             if (c->stream == g->stream || st != JC_OK)
@@ -611,7 +613,14 @@ int jc_group_iterate(jc_group* g, int64_t n)
     const int64_t rest = n - done;
     if (rest <= 0)
         return JC_OK;
-    if (!g->use_graphs)
+    int64_t launches = 0;                         // of the rest of the window
+    for (const Class& k : g->classes)
+        if (g->resident)
+            for (int q = 0; q < jc::kResidentVariants; ++q)
+                launches += !k.itemsr[q].empty();
+        else
+            launches += g->three_step ? rest / 3 + (rest % 3 != 0) : g->two_step ? (rest + 1) / 2 : rest;
+    if (!g->use_graphs || launches < kGraphMinLaunches)
         return group_run(g, rest);
     // graph of `rest` sweeps from the current launch parity; the d copy
     // of refinement members alternates with the launch parity
@@ -739,17 +748,21 @@ int jc_group_residuals(jc_group* g, double* host_l2)
             g->members[m]->ir_phase = 1;
     }
     const int nm = (int)g->members.size();
-    st = ghip(jc::launch_reduce(g->d_partials(), g->d_lohi(), nm, g->d_out(), g->stream), "reduce");
-    if (st == JC_OK)
-        st = ghip(hipMemcpyAsync(g->h_out, g->d_out(), sizeof(double) * nm, hipMemcpyDeviceToHost, g->stream),
+    const uint64_t seq = ++g->check_seq;
+    st = ghip(jc::launch_reduce(g->d_partials(), g->d_lohi(), nm, g->d_out(), g->h_out, seq, g->stream), "reduce");
+    if (st == JC_OK && !g->h_out)
+        st = ghip(hipMemcpyAsync(g->h_out_plain.data(), g->d_out(), sizeof(double) * nm, hipMemcpyDeviceToHost,
+                                 g->stream),
                   "copy residuals");
     if (st == JC_OK)
         st = ghip(hipStreamSynchronize(g->stream), "hipStreamSynchronize");
+    if (st == JC_OK && g->h_out)
+        st = ghip(wait_sums(g->stream, g->h_out, nm, seq), "residual sums");
     if (st != JC_OK)
         return st;
     int bad = -1;
     for (int m = 0; m < nm; ++m) {
-        host_l2[m] = std::sqrt(g->h_out[m]);
+        host_l2[m] = std::sqrt(g->h_out ? g->h_out[m].sum : g->h_out_plain[m]);
         if (!std::isfinite(host_l2[m]) && bad < 0)
             bad = m;
     }
@@ -789,7 +802,7 @@ void jc_group_destroy(jc_group* g)
         (void)hipGraphExecDestroy(kv.second);
     for (hipEvent_t e : g->events)
         (void)hipEventDestroy(e);
-    if (g->h_out && g->h_out != g->h_out_plain.data())
+    if (g->h_out)
         (void)hipHostFree(g->h_out);
     if (g->static_dev >= 0) {
         std::lock_guard<std::mutex> lock(static_mu);

@@ -12,6 +12,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -542,6 +543,30 @@ int drain_timing(jc_ctx* c)
     return JC_OK;
 }
 
+// The host looks at the sums themselves for a while -- a check of a small
+// grid is over within microseconds, and a wait for the stream adds several --
+// and then waits for the stream.
+hipError_t wait_sums(hipStream_t s, const jc::HostSum* host, int n, uint64_t seq)
+{
+    const auto start = std::chrono::steady_clock::now();
+    int m = 0;
+    for (int spin = 1;; ++spin) {
+        while (m < n && __atomic_load_n(&host[m].seq, __ATOMIC_ACQUIRE) == seq)
+            ++m;
+        if (m == n)
+            return hipSuccess;
+        if (spin % 64 == 0 && std::chrono::steady_clock::now() - start > std::chrono::microseconds(200))
+            break;
+    }
+    const hipError_t e = hipStreamSynchronize(s);
+    if (e != hipSuccess)
+        return e;
+    for (; m < n; ++m)
+        if (__atomic_load_n(&host[m].seq, __ATOMIC_ACQUIRE) != seq)
+            return hipErrorUnknown;
+    return hipSuccess;
+}
+
 // ------------------------------------------------------------------ steps
 
 int check_ready(jc_ctx* c)
@@ -883,15 +908,16 @@ int one_iteration(jc_ctx* c, bool resid)
     return do_sweep(c, false, resid);
 }
 
+// The sum of the residual partials, as the last work on the stream.
 int reduce_to_host(jc_ctx* c, double* sumsq)
 {
-    JC_HIP(jc::launch_reduce(c->d_partials(), c->d_ranges(), 1, c->d_result(), c->stream));
-    JC_HIP(hipMemcpyAsync(c->h_result, c->d_result(), sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    JC_HIP(hipStreamSynchronize(c->stream));
+    const uint64_t seq = ++c->check_seq;
+    JC_HIP(jc::launch_reduce(c->d_partials(), c->d_ranges(), 1, nullptr, c->h_result, seq, c->stream));
+    JC_HIP(wait_sums(c->stream, c->h_result, 1, seq));
     int st = drain_timing(c);
     if (st != JC_OK)
         return st;
-    *sumsq = c->h_result[0];
+    *sumsq = c->h_result[0].sum;
     return JC_OK;
 }
 
@@ -922,6 +948,7 @@ int residual_now(jc_ctx* c, double* l2)
     st = reduce_to_host(c, &s);
     if (st != JC_OK)
         return st;
+    JC_HIP(hipStreamSynchronize(c->stream));
     *l2 = std::sqrt(s);
     if (!std::isfinite(*l2))
         return fail(JC_ERR_NONFINITE, "residual is not finite");
@@ -971,9 +998,12 @@ int iterate_window(jc_ctx* c, int64_t n)
 {
     if (n <= 0)
         return JC_OK;
-    // a resident window is one launch already: nothing to capture
+    // A resident window is one launch already, and a window of a few launches
+    // is faster without a graph (kGraphMinLaunches).
+    const int64_t launches = c->opt.resident ? 1 : launches_for(n, c->depth());
+    const int64_t each = c->opt.mode == JC_MODE_STAGED && c->np() ? 4 : 1;   // pack, exchange, unpack, sweep
     const bool graphs = c->opt.use_graphs && c->stream != nullptr && !c->timing &&
-                        c->opt.exchange == JC_EXCHANGE_DEVICE && !c->opt.resident;
+                        c->opt.exchange == JC_EXCHANGE_DEVICE && launches * each >= kGraphMinLaunches;
     if (!graphs)
         return iterate_eager(c, n);
     // the priming pack of fused mode stays outside the graph
@@ -1015,7 +1045,6 @@ int iterate_window(jc_ctx* c, int64_t n)
     JC_HIP(hipGraphLaunch(found->second, c->stream));
     // the state after n iterations, as the eager path would leave it
     // (a two-sweep launch flips the copy once)
-    const int64_t launches = launches_for(n, c->depth());
     c->parity ^= (int)(launches & 1);
     c->iters += n;
     if (c->np()) {
@@ -1271,7 +1300,8 @@ int jc_bind(jc_ctx* c, void* dev_arena, size_t bytes, void* hip_stream)
     c->arena = static_cast<char*>(dev_arena);
     c->arena_bytes = bytes;
     c->stream = static_cast<hipStream_t>(hip_stream);
-    JC_HIP(hipHostMalloc(reinterpret_cast<void**>(&c->h_result), sizeof(double) * 4, hipHostMallocDefault));
+    JC_HIP(hipHostMalloc(reinterpret_cast<void**>(&c->h_result), sizeof(jc::HostSum), hipHostMallocDefault));
+    *c->h_result = jc::HostSum{0.0, 0};
     if (c->opt.overlap && c->np()) {
         // the halo stream of boundary-first iterations (default priority)
         JC_HIP(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
@@ -1556,6 +1586,7 @@ int jc_solve(jc_ctx* c, double rtol, int64_t max_iter, int64_t check_every, jc_s
             k += n;
         }
     }
+    JC_HIP(hipStreamSynchronize(c->stream));
     info->iters = c->iters - start;
     info->abs_resid = r;
     info->r0 = r0;
@@ -1658,7 +1689,8 @@ int jc_solve_ir(jc_ctx* c, int inner_sweeps, double rtol, int64_t max_inner, jc_
             }
             return s2;
         };
-        if (c->opt.use_graphs && c->stream != nullptr && !c->timing) {
+        if (c->opt.use_graphs && c->stream != nullptr && !c->timing &&
+            1 + launches_for(m - 1, c->depth()) >= kGraphMinLaunches) {
             // one graph per window length (key space apart from jc_iterate's)
             const auto key = std::make_pair(m, 2);
             auto found = c->graphs.find(key);
@@ -1698,6 +1730,7 @@ int jc_solve_ir(jc_ctx* c, int inner_sweeps, double rtol, int64_t max_inner, jc_
     // u stayed in its copy; its faces of slot `parity` are current
     c->ghost = c->np() ? GHOST_STALE : GHOST_CURRENT;
     c->fused_primed = c->np() > 0;
+    JC_HIP(hipStreamSynchronize(c->stream));
     info->iters = c->iters - start;
     info->abs_resid = r;
     info->r0 = r0;

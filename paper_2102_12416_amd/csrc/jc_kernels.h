@@ -80,9 +80,16 @@ hipError_t launch_ir_update(const BlockDesc* blocks, int nblocks, int64_t max_ro
                             int lo_dtype, hipStream_t s);
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
 
-// Sum partials[ranges[2m] .. ranges[2m+1]) in a fixed order into out[m], m < nmembers.
-hipError_t launch_reduce(const double* partials, const int32_t* ranges, int nmembers, double* out,
-                         hipStream_t s);
+// A residual sum in pinned host memory; seq is written after sum.
+struct HostSum {
+    double sum;
+    uint64_t seq;
+};
+
+// Sum partials[ranges[2m] .. ranges[2m+1]) in a fixed order, m < nmembers, into
+// out[m] (device memory), or into host[m] with seq where host is not null.
+hipError_t launch_reduce(const double* partials, const int32_t* ranges, int nmembers, double* out, HostSum* host,
+                         uint64_t seq, hipStream_t s);
 
 // Face pack (interior face plane of u[parity] -> pair buffer slot),
 // exchange (slot 0 -> slot 1), unpack (slot 1 -> ghost plane of u[parity]).

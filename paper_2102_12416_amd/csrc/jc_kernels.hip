@@ -69,13 +69,6 @@ template <typename T> struct Fld<T, FIELD_D> {
 
 struct NoRlo {};
 
-__device__ __forceinline__ double wave_sum(double v)
-{
-    for (int o = 32; o > 0; o >>= 1)
-        v = v + __shfl_xor(v, o, 64);
-    return v;
-}
-
 // Pacing.  The work-groups of a launch advance at different rates (a tile
 // on a Dirichlet face reads its ghosts from a compact column, other tiles
 // read their x halo from the neighbour tile's lines, work-groups sit at
@@ -1318,35 +1311,6 @@ k_resident(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items,
 }
 // ---- resident sweeps: end ----
 
-// Zero `words` 8-byte words at p (grid-stride).
-__global__ void __launch_bounds__(256)
-k_zero(uint64_t* __restrict__ p, int64_t words)
-{
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (int64_t)gridDim.x * 256)
-        *(uint64_t JC_GLOBAL*)(p + i) = 0;
-}
-
-// Fixed-order sum of one member's partials [ranges[2m], ranges[2m+1]):
-// each thread adds a strided subsequence in order, then a fixed tree over
-// the work-group.
-__global__ void __launch_bounds__(256)
-k_reduce(const double* __restrict__ partials, const int32_t* __restrict__ ranges,
-         double* __restrict__ out)
-{
-    const int m = blockIdx.x;
-    const int lo = ranges[2 * m], hi = ranges[2 * m + 1];
-    double t = 0.0;
-    for (int i = lo + (int)threadIdx.x; i < hi; i += 256)
-        t = t + partials[i];
-    __shared__ double w[4];
-    t = wave_sum(t);
-    if ((threadIdx.x & 63) == 0)
-        w[threadIdx.x >> 6] = t;
-    __syncthreads();
-    if (threadIdx.x == 0)
-        out[m] = ((w[0] + w[1]) + w[2]) + w[3];
-}
-
 }  // namespace
 
 hipError_t launch_sweep(const BlockDesc* blocks, const Item* items, int nitems, int parity,
@@ -1585,26 +1549,6 @@ hipError_t launch_ir_inner(const BlockDesc* blocks, const Item* items, int nitem
                                                            false, true, nullptr, s, pace);
     default: return hipErrorInvalidValue;
     }
-}
-
-hipError_t launch_zero(void* p, size_t bytes, hipStream_t s)
-{
-    const int64_t words = (int64_t)(bytes / 8);
-    if (words <= 0)
-        return hipSuccess;
-    int64_t blocks = (words + 255) / 256;
-    if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(k_zero, dim3((unsigned)blocks), dim3(256), 0, s, static_cast<uint64_t*>(p), words);
-    return hipGetLastError();
-}
-
-hipError_t launch_reduce(const double* partials, const int32_t* ranges, int nmembers, double* out,
-                         hipStream_t s)
-{
-    if (nmembers <= 0)
-        return hipSuccess;
-    hipLaunchKernelGGL(k_reduce, dim3(nmembers), dim3(256), 0, s, partials, ranges, out);
-    return hipGetLastError();
 }
 
 }  // namespace jc

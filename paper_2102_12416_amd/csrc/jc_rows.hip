@@ -1,7 +1,7 @@
 // Passes that touch every cell or face value once: global padded array <->
 // blocks, the refinement's first inner sweep and outer update, and the staged
-// halo exchange (pack, exchange, unpack; paper section 4.3).  All are bound
-// by memory.
+// halo exchange (pack, exchange, unpack; paper section 4.3), all bound by
+// memory; and the sums of residual partials.
 
 #include <hip/hip_runtime.h>
 
@@ -289,6 +289,55 @@ k_exchange(const PairDesc* __restrict__ pairs)
         b[i] = a[i];
 }
 
+// Zero `words` 8-byte words at p (grid-stride).
+__global__ void __launch_bounds__(256)
+k_zero(uint64_t* __restrict__ p, int64_t words)
+{
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (int64_t)gridDim.x * 256)
+        *(uint64_t JC_GLOBAL*)(p + i) = 0;
+}
+
+// Fixed-order sum of one member's partials [ranges[2m], ranges[2m+1]): each
+// thread adds a strided subsequence in order (eight loads in flight), then a
+// fixed tree over the work-group.  The sums go to `out` in device memory, or
+// (`host` not null) straight to pinned host memory, each followed by the
+// check's sequence number, which the host waits for: that spares the copy
+// and its launch, about 8 us of the 25 that a check of a small grid took.
+__global__ void __launch_bounds__(256)
+k_reduce(const double* __restrict__ partials, const int32_t* __restrict__ ranges, double* __restrict__ out,
+         HostSum* host, uint64_t seq)
+{
+    const int m = blockIdx.x;
+    const int lo = ranges[2 * m], hi = ranges[2 * m + 1];
+    double t = 0.0;
+    int i = lo + (int)threadIdx.x;
+    for (; i + 7 * 256 < hi; i += 8 * 256) {
+        double v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            v[k] = partials[i + k * 256];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            t = t + v[k];
+    }
+    for (; i < hi; i += 256)
+        t = t + partials[i];
+    __shared__ double w[4];
+    t = wave_sum(t);
+    if ((threadIdx.x & 63) == 0)
+        w[threadIdx.x >> 6] = t;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const double sum = ((w[0] + w[1]) + w[2]) + w[3];
+        if (host) {
+            host[m].sum = sum;
+            __hip_atomic_store(&host[m].seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        } else {
+            out[m] = sum;
+        }
+    }
+}
+
 // Lanes per row: the power of two in 8 .. 64 that covers the accesses of the
 // widest block's row, so that a wave covers several rows of a narrow block.
 int row_lanes(int accesses) { return accesses <= 8 ? 8 : accesses <= 16 ? 16 : accesses <= 32 ? 32 : 64; }
@@ -310,6 +359,26 @@ dim3 face_grid(int npairs, int64_t max_slow, int64_t max_fast)
 }
 
 }  // namespace
+
+hipError_t launch_zero(void* p, size_t bytes, hipStream_t s)
+{
+    const int64_t words = (int64_t)(bytes / 8);
+    if (words <= 0)
+        return hipSuccess;
+    int64_t blocks = (words + 255) / 256;
+    if (blocks > 4096) blocks = 4096;
+    hipLaunchKernelGGL(k_zero, dim3((unsigned)blocks), dim3(256), 0, s, static_cast<uint64_t*>(p), words);
+    return hipGetLastError();
+}
+
+hipError_t launch_reduce(const double* partials, const int32_t* ranges, int nmembers, double* out, HostSum* host,
+                         uint64_t seq, hipStream_t s)
+{
+    if (nmembers <= 0)
+        return hipSuccess;
+    hipLaunchKernelGGL(k_reduce, dim3(nmembers), dim3(256), 0, s, partials, ranges, out, host, seq);
+    return hipGetLastError();
+}
 
 hipError_t launch_pack(const BlockDesc* blocks, const PairDesc* pairs, int npairs, int max_slow, int max_fast,
                        int parity, int slot, hipStream_t s)

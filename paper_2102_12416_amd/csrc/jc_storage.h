@@ -39,6 +39,14 @@ __device__ __forceinline__ uint32_t f32_to_bf16(float f)
     return __builtin_isnan(f) ? quiet_nan : rounded;   // an unordered self-compare
 }
 
+// Fixed-order sum over the lanes of a wave.
+__device__ __forceinline__ double wave_sum(double v)
+{
+    for (int o = 32; o > 0; o >>= 1)
+        v = v + __shfl_xor(v, o, 64);
+    return v;
+}
+
 // Storage formats of a swept field: arithmetic type C, and loads / stores
 // of the 2-element aligned pair (x, x + 1) that one thread owns.
 template <typename T> struct Tr;
