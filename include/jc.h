@@ -291,8 +291,8 @@ int jc_solve_ir(jc_ctx* ctx, int inner_sweeps, double rtol, int64_t max_inner,
  * per launch (the same conditions and tiles; a count that is not a
  * multiple of three ends with a two-sweep launch or a single sweep);
  * bit 3 = resident sweeps: every jc_group_iterate window is one launch per
- * class and parity of the members' (nz + 1) / 2 with one work-group per
- * member, which keeps its member's block on chip for the whole window
+ * class with one work-group per member, which keeps its member's block on
+ * chip for the whole window
  * (members as for options.resident: one block of at most 32 planes,
  * (nx + 1) / 2 * ny <= 512, the LDS limit there, no refinement; else
  * JC_ERR_INVALID; not with bits 1 and 2; results bitwise the same).

@@ -33,7 +33,13 @@ __host__ __device__ __forceinline__ double div6_fast(double s)
 {
     const double y = 0x1.5555555555555p-3;
     const double q = s * y;
-    return __builtin_fma(__builtin_fma(-6.0, q, s), y, q);
+    double m = -6.0;
+#ifdef __HIP_DEVICE_COMPILE__
+    // in a scalar register: as a literal it forces the two-operand form of the
+    // multiply-add, and with it a copy of s
+    asm("" : "+s"(m));
+#endif
+    return __builtin_fma(__builtin_fma(m, q, s), y, q);
 }
 
 __host__ __device__ __forceinline__ float div6_fast(float s)
@@ -67,6 +73,39 @@ __host__ __device__ __forceinline__ void div6_pair(C sa, C sb, C& va, C& vb)
     if (__builtin_expect(ra || rb, 0)) {
         va = ra ? sa / C(6) : va;
         vb = rb ? sb / C(6) : vb;
+    }
+}
+
+// Four values with one such branch; on the device the four independent steps
+// of each round stay together.
+__host__ __device__ __forceinline__ void div6_quad(double sa, double sb, double sc, double sd, double& va, double& vb,
+                                                   double& vc, double& vd)
+{
+    const double y = 0x1.5555555555555p-3;
+    double m = -6.0;
+#ifdef __HIP_DEVICE_COMPILE__
+    asm("" : "+s"(m));
+#define JC_ROUND() __builtin_amdgcn_sched_barrier(0)
+#else
+#define JC_ROUND()
+#endif
+    const double qa = sa * y, qb = sb * y, qc = sc * y, qd = sd * y;
+    JC_ROUND();
+    const double ea = __builtin_fma(m, qa, sa), eb = __builtin_fma(m, qb, sb), ec = __builtin_fma(m, qc, sc),
+                 ed = __builtin_fma(m, qd, sd);
+    JC_ROUND();
+    va = __builtin_fma(ea, y, qa);
+    vb = __builtin_fma(eb, y, qb);
+    vc = __builtin_fma(ec, y, qc);
+    vd = __builtin_fma(ed, y, qd);
+    JC_ROUND();
+#undef JC_ROUND
+    const bool ra = div6_redo(va), rb = div6_redo(vb), rc = div6_redo(vc), rd = div6_redo(vd);
+    if (__builtin_expect(ra || rb || rc || rd, 0)) {
+        va = ra ? sa / 6.0 : va;
+        vb = rb ? sb / 6.0 : vb;
+        vc = rc ? sc / 6.0 : vc;
+        vd = rd ? sd / 6.0 : vd;
     }
 }
 

@@ -40,12 +40,11 @@ struct Class {
     size_t item2_0 = 0;              // first joint two-sweep item
     std::vector<Item> items2;        // two-sweep tiles (groups that sweep twice per launch)
     std::vector<int> members;
-    // resident sweeps: one item per member, split by launch variant (the
-    // kernel's step schedule depends on the parity of (nz + 1) / 2)
-    std::vector<Item> itemsr[jc::kResidentVariants];
-    size_t itemr0[jc::kResidentVariants] = {};       // first joint resident item of each split
-    int max_pairs[jc::kResidentVariants] = {}, max_nz[jc::kResidentVariants] = {};
-    int64_t lds[jc::kResidentVariants] = {};
+    // resident sweeps: one item per member, the largest blocks first, so
+    // that the last work-groups to start are the shortest
+    std::vector<Item> itemsr;
+    size_t itemr0 = 0;                             // first joint resident item
+    jc::ResidentShape shape;                       // of the members' blocks
 };
 
 // Two-sweep tiles of a group: 64 cells by kGroupTwoStepRows rows, and at
@@ -202,20 +201,15 @@ int group_sweep3(jc_group* g)
     return JC_OK;
 }
 
-// n sweeps of every member in one launch per class and launch variant
-// (resident groups).
+// n sweeps of every member in one launch per class (resident groups).
 int group_resident(jc_group* g, int64_t n)
 {
-    for (const Class& k : g->classes)
-        for (int q = 0; q < jc::kResidentVariants; ++q) {
-            if (k.itemsr[q].empty())
-                continue;
-            const hipError_t e = jc::launch_resident(g->d_desc(), g->d_itemsr() + k.itemr0[q], (int)k.itemsr[q].size(),
-                                                     k.max_pairs[q], k.max_nz[q], (size_t)k.lds[q], q, g->parity,
-                                                     (int)n, k.src, g->stream);
-            if (e != hipSuccess)
-                return ghip(e, "group resident launch");
-        }
+    for (const Class& k : g->classes) {
+        const hipError_t e = jc::launch_resident(g->d_desc(), g->d_itemsr() + k.itemr0, (int)k.itemsr.size(), k.shape,
+                                                 g->parity, (int)n, k.src, g->stream);
+        if (e != hipSuccess)
+            return ghip(e, "group resident launch");
+    }
     return JC_OK;
 }
 
@@ -389,16 +383,13 @@ int jc_group_create(jc_ctx* const* ctxs, int n, void* hip_stream, int flags, con
             }
             if (g->resident) {
                 const int64_t* bn = c->blocks[0].n;
-                const int q = jc::resident_variant(bn[2]);
                 Item it{};
                 it.block = (int32_t)g->desc.size();
                 it.zlen = (int32_t)bn[2];
                 it.flip = c->parity;
                 it.owner = m;
-                k.itemsr[q].push_back(it);
-                k.max_pairs[q] = std::max<int>(k.max_pairs[q], (int)((bn[0] + 1) / 2 * bn[1]));
-                k.max_nz[q] = std::max<int>(k.max_nz[q], (int)bn[2]);
-                k.lds[q] = std::max(k.lds[q], jc::resident_lds_bytes(bn[0], bn[1], bn[2]));
+                k.itemsr.push_back(it);
+                k.shape.add(bn[0], bn[1], bn[2]);
             }
             g->desc.insert(g->desc.end(), c->hdesc.begin(), c->hdesc.end());
             g->items.insert(g->items.end(), k.items.begin() + first, k.items.end());
@@ -408,10 +399,12 @@ int jc_group_create(jc_ctx* const* ctxs, int n, void* hip_stream, int flags, con
         k.bend = (int)g->desc.size();
         k.item2_0 = g->items2.size();
         g->items2.insert(g->items2.end(), k.items2.begin(), k.items2.end());
-        for (int q = 0; q < jc::kResidentVariants; ++q) {
-            k.itemr0[q] = g->itemsr.size();
-            g->itemsr.insert(g->itemsr.end(), k.itemsr[q].begin(), k.itemsr[q].end());
-        }
+        std::stable_sort(k.itemsr.begin(), k.itemsr.end(), [&](const Item& a, const Item& b) {
+            const int32_t *p = g->desc[a.block].n, *q = g->desc[b.block].n;
+            return (int64_t)p[0] * p[1] * p[2] > (int64_t)q[0] * q[1] * q[2];
+        });
+        k.itemr0 = g->itemsr.size();
+        g->itemsr.insert(g->itemsr.end(), k.itemsr.begin(), k.itemsr.end());
     }
     if (g->desc.size() > 65535 || g->items.size() > ((size_t)1 << 30) || g->items2.size() > ((size_t)1 << 30)) {
         delete g;
@@ -614,12 +607,8 @@ int jc_group_iterate(jc_group* g, int64_t n)
     if (rest <= 0)
         return JC_OK;
     int64_t launches = 0;                         // of the rest of the window
-    for (const Class& k : g->classes)
-        if (g->resident)
-            for (int q = 0; q < jc::kResidentVariants; ++q)
-                launches += !k.itemsr[q].empty();
-        else
-            launches += g->three_step ? rest / 3 + (rest % 3 != 0) : g->two_step ? (rest + 1) / 2 : rest;
+    for (size_t i = 0; i < g->classes.size(); ++i)
+        launches += g->resident ? 1 : g->three_step ? rest / 3 + (rest % 3 != 0) : g->two_step ? (rest + 1) / 2 : rest;
     if (!g->use_graphs || launches < kGraphMinLaunches)
         return group_run(g, rest);
     // graph of `rest` sweeps from the current launch parity; the d copy

@@ -799,11 +799,11 @@ int do_sweep2(jc_ctx* c)
 int do_resident(jc_ctx* c, int64_t n)
 {
     const auto& b = c->blocks[0];
-    const int nx = (int)b.n[0], ny = (int)b.n[1], nz = (int)b.n[2];
+    jc::ResidentShape shape;
+    shape.add(b.n[0], b.n[1], b.n[2]);
     int st = timed(c, JC_K_RESIDENT, [&] {
-        return jc::launch_resident(c->d_blocks(), nullptr, 1, (nx + 1) / 2 * ny, nz,
-                                   (size_t)jc::resident_lds_bytes(nx, ny, nz), jc::resident_variant(nz), c->parity, (int)n,
-                                   c->opt.with_source != 0, c->stream);
+        return jc::launch_resident(c->d_blocks(), nullptr, 1, shape, c->parity, (int)n, c->opt.with_source != 0,
+                                   c->stream);
     });
     if (st != JC_OK)
         return st;

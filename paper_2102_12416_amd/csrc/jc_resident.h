@@ -27,9 +27,33 @@ inline constexpr bool resident_fits(int64_t nx, int64_t ny, int64_t nz)
            resident_lds_bytes(nx, ny, nz) <= kResidentMaxLds;
 }
 
-// Launch variant of a block of nz planes (the kernel's step schedule): the
-// parity of its number of two-plane steps per sweep, (nz + 1) / 2.
-constexpr int kResidentVariants = 2;
-inline constexpr int resident_variant(int64_t nz) { return (int)(((nz + 1) / 2) & 1); }
+// Bytes of one of the kernel's four plane buffers with its ghost rings: the
+// pairs (rounded up to whole waves) and a quarter of the planes' rings.  The
+// largest over all blocks that fit is 24592 (1024 x 1 x 1).
+inline constexpr int64_t resident_region_bytes(int64_t nx, int64_t ny, int64_t nz)
+{
+    const int64_t ep = (nx + 1) / 2;
+    return 16 * ((ep * ny + 63) / 64 * 64 + (nz + 3) / 4 * (2 * ep + ny));
+}
+
+// Buffer sizes the kernel is built for: up to 16^3 (eight work-groups on a
+// compute unit), up to 32^3, and every shape that fits.
+constexpr int kResidentRegions[3] = {4096, 16384, 24832};
+
+// What a launch has to hold: the largest of each over the blocks it sweeps.
+struct ResidentShape {
+    int pairs = 0, planes = 0;
+    int64_t region = 0;
+    bool odd = false;           // some nx is odd
+
+    void add(int64_t nx, int64_t ny, int64_t nz)
+    {
+        const int64_t r = resident_region_bytes(nx, ny, nz);
+        pairs = (int)((nx + 1) / 2 * ny) > pairs ? (int)((nx + 1) / 2 * ny) : pairs;
+        planes = (int)nz > planes ? (int)nz : planes;
+        region = r > region ? r : region;
+        odd = odd || (nx & 1);
+    }
+};
 
 }  // namespace jc
