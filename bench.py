@@ -197,21 +197,21 @@ def recorded_traffic(workload, mode, tile, pace=0):
 
 def sweep_source_sha256(kernel="k_sweep"):
     """Fingerprint of a sweep kernel: its region of jc_kernels.hip (the
-    one-sweep kernel with the helpers it defines; the two-sweep kernel
-    also with those helpers) plus the shared table definitions and the
-    division helpers it includes."""
+    one-sweep kernel) or jc_temporal.hip (the two-sweep kernel) plus the
+    shared table definitions and helpers it includes."""
     import hashlib
     csrc = os.path.join(ROOT, "paper_2102_12416_amd", "csrc")
-    text = open(os.path.join(csrc, "jc_kernels.hip")).read()
-    a = text.index("// ---- sweep kernel: begin")
-    b = text.index("// ---- sweep kernel: end")
-    h = hashlib.sha256(text[a:b].encode())
     if kernel == "k_sweep2":
-        c = text.index("// ---- two-step sweep (temporal blocking): begin")
-        d = text.index("// ---- two-step sweep: end")
-        h.update(text[c:d].encode())
-    h.update(open(os.path.join(csrc, "jc_types.h"), "rb").read())
-    h.update(open(os.path.join(csrc, "jc_div6.h"), "rb").read())
+        text = open(os.path.join(csrc, "jc_temporal.hip")).read()
+        a = text.index("// ---- two-step sweep (temporal blocking): begin")
+        b = text.index("// ---- two-step sweep: end")
+    else:
+        text = open(os.path.join(csrc, "jc_kernels.hip")).read()
+        a = text.index("// ---- sweep kernel: begin")
+        b = text.index("// ---- sweep kernel: end")
+    h = hashlib.sha256(text[a:b].encode())
+    for name in ("jc_types.h", "jc_div6.h", "jc_storage.h", "jc_sweep.h"):
+        h.update(open(os.path.join(csrc, name), "rb").read())
     return h.hexdigest()
 
 

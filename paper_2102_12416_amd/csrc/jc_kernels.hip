@@ -20,72 +20,14 @@
 
 #include "jc_div6.h"
 #include "jc_kernels.h"
-#include "jc_storage.h"
+#include "jc_sweep.h"
 
 namespace jc {
 
 namespace {
 
-// Work-groups are dispatched round-robin over the 8 XCDs of the chip
-// (work-group i to XCD i mod 8).  Give each XCD a contiguous range of
-// logical tiles so that tiles sharing halo rows run under the same L2.
-__device__ __forceinline__ int logical_block(int bid, int nblocks)
-{
-    const int per = nblocks >> 3;           // nblocks is a multiple of 8
-    return (bid & 7) * per + (bid >> 3);
-}
-
 // ---- sweep kernel: begin (its source is fingerprinted with recorded counters) ----
-// Which arrays of a block a sweep works on: the iterate u (with source b)
-// or the refinement correction d (with source r_lo).
-enum { FIELD_U = 0, FIELD_D = 1 };
-
-template <typename T, int FIELD> struct Fld;
-
-template <typename T> struct Fld<T, FIELD_U> {
-    __device__ static const T* src(const BlockDesc* B, int p) { return B->u[p]; }
-    __device__ static T* dst(const BlockDesc* B, int p) { return B->u[p ^ 1]; }
-    __device__ static const T* source(const BlockDesc* B) { return B->b; }
-    __device__ static const T* gin(const BlockDesc* B, int f, int s) { return B->gin[f][s]; }
-    __device__ static T* gout(const BlockDesc* B, int f, int s) { return B->gout[f][s]; }
-    __device__ static const T* xg(const BlockDesc* B, int f) { return B->xg[f]; }
-    __device__ static int64_t pitch(const BlockDesc* B) { return B->pitch; }
-    __device__ static int64_t plane(const BlockDesc* B) { return B->plane; }
-};
-
-template <typename T> struct Fld<T, FIELD_D> {
-    __device__ static const T* src(const BlockDesc* B, int p) { return static_cast<const T*>(B->d[p]); }
-    __device__ static T* dst(const BlockDesc* B, int p) { return static_cast<T*>(B->d[p ^ 1]); }
-    __device__ static const T* source(const BlockDesc* B) { return static_cast<const T*>(B->rlo); }
-    __device__ static const T* gin(const BlockDesc* B, int f, int s)
-    {
-        return static_cast<const T*>(B->lgin[f][s]);
-    }
-    __device__ static T* gout(const BlockDesc* B, int f, int s) { return static_cast<T*>(B->lgout[f][s]); }
-    __device__ static const T* xg(const BlockDesc* B, int f) { return static_cast<const T*>(B->lxg[f]); }
-    __device__ static int64_t pitch(const BlockDesc* B) { return B->lpitch; }
-    __device__ static int64_t plane(const BlockDesc* B) { return B->lplane; }
-};
-
 struct NoRlo {};
-
-// Pacing.  The work-groups of a launch advance at different rates (a tile
-// on a Dirichlet face reads its ghosts from a compact column, other tiles
-// read their x halo from the neighbour tile's lines, work-groups sit at
-// different distances from the memory they stream), and the launch ends
-// with the slowest: measured on the 512^3 launch of 256 tiles, they took
-// 359-396 us, so the compute units of the fast ones idled through the
-// tail.  With a pace, a work-group waits before plane step k until k *
-// pace ticks of the chip's constant 100 MHz clock have passed since it
-// started: the fast ones are held to the pace and the memory traffic of
-// the slow ones runs without their competition, so all finish together.
-// The pace is tuned by timing (jc_autotune); 0 = none.  Each wait is
-// bounded (4096 short sleeps), and results do not depend on it.
-__device__ __forceinline__ void pace_wait(uint64_t due)
-{
-    for (int i = 0; i < 4096 && __builtin_amdgcn_s_memrealtime() < due; ++i)
-        __builtin_amdgcn_s_sleep(1);
-}
 
 // Planes of loads a sweep keeps in flight ahead of the plane it computes:
 // three.  For binary64 fields at one 16-wave work-group per CU two planes
@@ -507,519 +449,6 @@ hipError_t sweep_tiles(const BlockDesc* blocks, const Item* items, int nitems, i
 
 // ---- sweep kernel: end ----
 
-// ---- two-step sweep (temporal blocking): begin (fingerprinted with recorded counters) ----
-// Two Jacobi sweeps of the single block of a context without face pairs
-// per launch: iterate k is read from copy p and iterate k + 2 written to
-// copy p ^ 1; iterate k + 1 lives only in LDS and registers.  T / FIELD as
-// for k_sweep: the binary64 iterate u (source b), or the refinement
-// correction d in its storage format (source r_lo, zero ghosts), whose
-// iterate k + 1 is rounded to that format as a stored sweep would leave
-// it.  Each cell's two updates take the same sums in the same order as
-// two one-step sweeps, so the result is bitwise the same; HBM moves one
-// read and one write per cell for two sweeps instead of two of each.
-//
-// A work-group owns a tile of 2 TXP x cells by TY rows and a z range, and
-// marches along z as the one-step sweep does.  Iterate k + 1 is needed on
-// the tile and on a one-cell ring around it, so iterate k is loaded on a
-// two-cell ring: one aligned pair per thread over (TXP + 2) pairs by (TY +
-// 4) rows.  The first TXP * TY threads (whole waves) own the tile's pairs,
-// the next 4 (TXP + 2) the two rows above and the two rows below it, the
-// next 2 TY the pair left and the pair right of each tile row.  At plane
-// step s every thread writes iterate k of its pair at plane s into LDS,
-// the work-group synchronises once, every thread computes iterate k + 1 of
-// its pair at plane s (a ghost cell keeps its value: the context has no
-// face pairs, so every ghost is a fixed boundary value) into a second LDS
-// plane, and the tile threads compute iterate k + 2 at plane s - 1 from
-// the previous step's second plane.  Both LDS planes are double-buffered
-// by step parity.  Values at cells two steps out of the block (the
-// outermost ring of a tile on the block edge) are clamped loads that only
-// feed discarded results.
-// A value of the arithmetic type rounded to the storage format and back:
-// iterate k + 1 is stored between the two sweeps of a one-sweep-per-launch
-// run, so the second sweep must read it at storage precision.
-template <typename T> __device__ __forceinline__ typename Tr<T>::C storage_round(typename Tr<T>::C v) { return v; }
-template <> __device__ __forceinline__ float storage_round<bf16>(float v) { return bf16_to_f32(f32_to_bf16(v)); }
-
-//
-// Work: with items null, the tiles of blocks[0] (tiles_x by tiles_y per z
-// chunk, nch chunks, ntiles in all) numbered from the work-group index;
-// otherwise the work list items[0 .. ntiles), whose tiles must be 2 TXP
-// cells by TY rows, each with its block and ping-pong flip (groups).
-// A pair of arithmetic values as one LDS access (16 bytes in binary64).
-template <typename C> struct Pair2;
-template <> struct Pair2<double> { using V = v2d; };
-template <> struct Pair2<float> { using V = v2f; };
-
-template <typename T, int FIELD, int TXP, int TY, bool SRC>
-__global__ void __launch_bounds__(((TXP + 2) * (TY + 4) + 63) / 64 * 64)
-k_sweep2(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items, int parity, int tiles_x,
-         int tiles_y, int nch, int ntiles, uint32_t pace)
-{
-    using C = typename Tr<T>::C;
-    using F = Fld<T, FIELD>;
-    constexpr int EP = TXP + 2;                   // pairs of an extended row
-    constexpr int ER = TY + 4;                    // extended rows
-    constexpr int NTILE = TXP * TY;               // tile threads
-    static_assert(NTILE % 64 == 0, "tile threads are whole waves");
-    using V = typename Pair2<C>::V;
-    // LDS row: two pad cells, 2 EP cells, two pad cells, so that every
-    // thread's pair is one aligned vector: a pair is written with one
-    // access and its neighbours' pairs are read with one access each
-    constexpr int LW = 2 * EP + 4;
-    constexpr int LN = (ER + 2) * LW;             // LDS plane: pad row, ER rows, pad row
-    __shared__ V A[2][LN / 2 + 1];                // iterate k; pair LN / 2: sink of idle lanes
-    __shared__ V Bn[2][LN / 2 + 1];               // iterate k + 1
-
-    const int id = logical_block(blockIdx.x, gridDim.x);
-    if (id >= ntiles)
-        return;                                   // uniform over the work-group
-    const uint64_t pace_t0 = pace ? __builtin_amdgcn_s_memrealtime() : 0;
-    const BlockDesc* B = blocks;
-    int p = parity, x0, y0, zf, zl;
-    if (items) {
-        const Item it = items[id];
-        B = blocks + it.block;
-        p = parity ^ it.flip;
-        x0 = it.x0;
-        y0 = it.y0;
-        zf = it.z0 + 1;
-        zl = it.z0 + it.zlen;
-    } else {
-        const int per = tiles_x * tiles_y;
-        const int chunk = id / per;
-        const int nzb = B->n[2];
-        x0 = (id % tiles_x) * (2 * TXP);
-        y0 = ((id % per) / tiles_x) * TY;
-        zf = (int)((int64_t)chunk * nzb / nch) + 1;
-        zl = (int)((int64_t)(chunk + 1) * nzb / nch);
-    }
-    const int nx = B->n[0], ny = B->n[1], nz = B->n[2];
-
-    // this thread's pair (j, r) of the extended region
-    const int t = threadIdx.x;
-    int j = 0, r = 0;
-    bool live = true;
-    if (t < NTILE) {
-        j = 1 + t % TXP;
-        r = 2 + t / TXP;
-    } else {
-        int q = t - NTILE;
-        if (q < 2 * EP) {
-            j = q % EP;
-            r = q / EP;
-        } else if ((q -= 2 * EP) < 2 * EP) {
-            j = q % EP;
-            r = TY + 2 + q / EP;
-        } else if ((q -= 2 * EP) < 2 * TY) {
-            j = (q & 1) ? EP - 1 : 0;
-            r = 2 + (q >> 1);
-        } else {
-            live = false;
-        }
-    }
-    const bool tile = t < NTILE;                  // uniform over each wave
-    const int xs = x0 - 1 + 2 * j;                // cells xs, xs + 1 (xs odd, >= -1)
-    const int ye = y0 - 1 + r;
-    const int xs_c = min(xs, nx | 1);             // last pair holding a cell <= nx + 1
-    const int ye_c = min(max(ye, 0), ny + 1);
-    const bool y_in = ye >= 1 && ye <= ny;
-    const bool in_a = live && y_in && xs >= 1 && xs <= nx;
-    const bool in_b = live && y_in && xs + 1 >= 1 && xs + 1 <= nx;
-    const bool a_ok = tile && ye <= ny && xs <= nx;   // tile cells in the block: stored
-    const bool b_ok = tile && ye <= ny && xs + 1 <= nx;
-    const int64_t pitch = F::pitch(B);
-    const int64_t plane = F::plane(B);
-    const int64_t rowoff = (int64_t)ye_c * pitch + xs_c;
-    const T* __restrict__ col = F::src(B, p) + rowoff;
-    const T* __restrict__ scol = SRC ? F::source(B) + rowoff : nullptr;
-    T* __restrict__ dst = F::dst(B, p) + rowoff;
-
-    const int pn = (r + 1) * (LW / 2) + j + 1;    // LDS pair of cells xs, xs + 1
-    const int pw = live ? pn : LN / 2;            // the pair this thread writes
-
-    // register rings: iterate k and the source of plane s in slot
-    // (s - zf + 1) mod RS, loads issued PD planes ahead; iterate k + 1 of
-    // plane s in slot (s - zf + 1) mod 3
-    constexpr int PD = 3;
-    constexpr int RS = 6;
-    const int zhi = min(zl + 2, nz + 1);          // last plane read
-    C ua[RS], ub[RS], ba[RS], bb[RS], va[3], vb[3];
-#pragma unroll
-    for (int k = 0; k < RS; ++k)
-        ba[k] = bb[k] = C(0);
-    va[0] = vb[0] = va[1] = vb[1] = va[2] = vb[2] = C(0);
-    Tr<T>::ld(col + (int64_t)max(zf - 2, 0) * plane, ua[RS - 1], ub[RS - 1]);
-#pragma unroll
-    for (int k = 0; k < PD; ++k) {
-        const int64_t zk = (int64_t)min(zf - 1 + k, zhi) * plane;
-        Tr<T>::ld(col + zk, ua[k], ub[k]);
-        if (SRC)
-            Tr<T>::ld(scol + zk, ba[k], bb[k]);
-    }
-
-    const int s_first = zf - 1;
-    auto step = [&](int s, auto kc, auto two) {
-        constexpr int K = decltype(kc)::value;
-        constexpr bool TWO = decltype(two)::value;
-        constexpr int SM = (K + RS - 1) % RS, SC = K, SP = (K + 1) % RS, SQ = (K + PD) % RS;
-        constexpr int VC = K % 3, VM = (K + 2) % 3, VMM = (K + 1) % 3;
-        constexpr int HC = K & 1;
-        if (pace)
-            pace_wait(pace_t0 + (uint64_t)(s - s_first) * pace);
-        const int64_t zq = (int64_t)min(s + PD, zhi) * plane;
-        Tr<T>::ld(col + zq, ua[SQ], ub[SQ]);
-        if (SRC)
-            Tr<T>::ld(scol + zq, ba[SQ], bb[SQ]);
-        V* const Ak = A[HC];
-        Ak[pw] = V{ua[SC], ub[SC]};
-        __syncthreads();
-        // iterate k + 1 at plane s
-        const V ym = Ak[pn - LW / 2], yp = Ak[pn + LW / 2], xm = Ak[pn - 1], xp = Ak[pn + 1];
-        C sa = xm.y + ub[SC];
-        sa = sa + ym.x;
-        sa = sa + yp.x;
-        sa = sa + ua[SM];
-        sa = sa + ua[SP];
-        C sb = ua[SC] + xp.x;
-        sb = sb + ym.y;
-        sb = sb + yp.y;
-        sb = sb + ub[SM];
-        sb = sb + ub[SP];
-        C na, nb;
-        if (SRC)
-            div6_pair(sa + ba[SC], sb + bb[SC], na, nb);
-        else
-            div6_pair(sa, sb, na, nb);
-        const bool z_in = s >= 1 && s <= nz;
-        va[VC] = (in_a && z_in) ? storage_round<T>(na) : ua[SC];
-        vb[VC] = (in_b && z_in) ? storage_round<T>(nb) : ub[SC];
-        Bn[HC][pw] = V{va[VC], vb[VC]};
-        // iterate k + 2 at plane s - 1
-        if (TWO && tile) {
-            const V* const Bk = Bn[HC ^ 1];
-            const V ym2 = Bk[pn - LW / 2], yp2 = Bk[pn + LW / 2], xm2 = Bk[pn - 1], xp2 = Bk[pn + 1];
-            C qa = xm2.y + vb[VM];
-            qa = qa + ym2.x;
-            qa = qa + yp2.x;
-            qa = qa + va[VMM];
-            qa = qa + va[VC];
-            C qb = va[VM] + xp2.x;
-            qb = qb + ym2.y;
-            qb = qb + yp2.y;
-            qb = qb + vb[VMM];
-            qb = qb + vb[VC];
-            C wa2, wb2;
-            if (SRC)
-                div6_pair(qa + ba[SM], qb + bb[SM], wa2, wb2);
-            else
-                div6_pair(qa, qb, wa2, wb2);
-            // past the last cell of a row the pair's second slot is the
-            // x = nx + 1 ghost: write back the value it holds
-            wb2 = b_ok ? wb2 : ub[SM];
-            if (a_ok)
-                Tr<T>::stn(dst + (int64_t)(s - 1) * plane, wa2, wb2);
-        }
-    };
-    using F_ = std::false_type;
-    using T_ = std::true_type;
-#define JC_STEP2(k) step(s + (k), std::integral_constant<int, ((k) + 2) % RS>{}, T_{})
-    int s = zf - 1;
-    step(s, std::integral_constant<int, 0>{}, F_{});
-    step(s + 1, std::integral_constant<int, 1>{}, F_{});
-    s += 2;
-    const int s_end = zl + 1;
-    for (; s + 5 <= s_end; s += 6) {
-        JC_STEP2(0);
-        JC_STEP2(1);
-        JC_STEP2(2);
-        JC_STEP2(3);
-        JC_STEP2(4);
-        JC_STEP2(5);
-    }
-    if (s <= s_end) JC_STEP2(0);
-    if (s + 1 <= s_end) JC_STEP2(1);
-    if (s + 2 <= s_end) JC_STEP2(2);
-    if (s + 3 <= s_end) JC_STEP2(3);
-    if (s + 4 <= s_end) JC_STEP2(4);
-#undef JC_STEP2
-}
-// ---- two-step sweep: end ----
-
-// ---- three-step sweep (temporal blocking): begin ----
-// Three Jacobi sweeps per launch: iterate k from copy p, iterate k + 3 to
-// copy p ^ 1; iterates k + 1 and k + 2 live only in LDS and registers.
-// The construction of k_sweep2 one level deeper.  Iterate k is loaded on
-// a three-cell ring around the tile: TXP + 4 pairs (cells x0 - 3 ..
-// x0 + 2 TXP + 4) by TY + 6 rows, one aligned pair per thread.  At plane
-// step s every thread writes iterate k of its pair at plane s into LDS,
-// the work-group synchronises once, and then
-//  - every thread computes iterate k + 1 of its pair at plane s (valid on
-//    the tile and a two-cell ring; the outermost values, which would need
-//    cells further out, are never read) into LDS plane B;
-//  - the threads of the tile and of its one-pair / one-row ring ("mid"
-//    threads) compute iterate k + 2 at plane s - 1 from B of the previous
-//    step into LDS plane C;
-//  - the tile threads compute iterate k + 3 at plane s - 2 from C of the
-//    previous step and store it.
-// A ghost cell keeps its value at every level (the context has no face
-// pairs: every ghost is a fixed boundary value), and iterates k + 1 and
-// k + 2 are rounded to the storage format as stored sweeps would leave
-// them, so each cell takes the same sums in the same order as in three
-// one-step sweeps: the result is bitwise the same.  The three LDS planes
-// are double-buffered by step parity, so one barrier per step suffices.
-// Thread order: tile threads (whole waves), then the mid ring (rows y0 and
-// y0 + TY + 1 over pairs 1 .. TXP + 2, then pairs 1 and TXP + 2 of the tile
-// rows), then the rest of the two-cell ring (rows y0 - 1 and y0 + TY + 2
-// over pairs 1 .. TXP + 2), then the third ring (the outermost rows, then
-// pairs 0 and TXP + 3 of the other rows), whose iterate k + 1 is not
-// needed.  Work as for k_sweep2 (items null: the
-// tiles of blocks[0]; else a work list of 2 TXP x TY tiles).
-template <typename T, int FIELD, int TXP, int TY, bool SRC>
-__global__ void __launch_bounds__(((TXP + 4) * (TY + 6) + 63) / 64 * 64)
-k_sweep3(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items, int parity, int tiles_x,
-         int tiles_y, int nch, int ntiles, uint32_t pace)
-{
-    using C = typename Tr<T>::C;
-    using F = Fld<T, FIELD>;
-    constexpr int EP = TXP + 4;                   // pairs of an extended row
-    constexpr int ER = TY + 6;                    // extended rows
-    constexpr int NTILE = TXP * TY;               // tile threads
-    constexpr int NMID = NTILE + 2 * (TXP + 2) + 2 * TY;
-    constexpr int NL1 = NMID + 2 * (TXP + 2);
-    static_assert(NTILE % 64 == 0, "tile threads are whole waves");
-    using V = typename Pair2<C>::V;
-    // LDS row: two pad cells, 2 EP cells, two pad cells, so that every
-    // thread's pair is one aligned vector: a pair is written with one
-    // access and its neighbours' pairs are read with one access each
-    constexpr int LW = 2 * EP + 4;
-    constexpr int LN = (ER + 2) * LW;             // LDS plane: pad row, ER rows, pad row
-    __shared__ V A[2][LN / 2 + 1];                // iterate k; pair LN / 2: sink of idle lanes
-    __shared__ V Bn[2][LN / 2 + 1];               // iterate k + 1
-    __shared__ V Cn[2][LN / 2 + 1];               // iterate k + 2
-
-    const int id = logical_block(blockIdx.x, gridDim.x);
-    if (id >= ntiles)
-        return;                                   // uniform over the work-group
-    const uint64_t pace_t0 = pace ? __builtin_amdgcn_s_memrealtime() : 0;
-    const BlockDesc* B = blocks;
-    int p = parity, x0, y0, zf, zl;
-    if (items) {
-        const Item it = items[id];
-        B = blocks + it.block;
-        p = parity ^ it.flip;
-        x0 = it.x0;
-        y0 = it.y0;
-        zf = it.z0 + 1;
-        zl = it.z0 + it.zlen;
-    } else {
-        const int per = tiles_x * tiles_y;
-        const int chunk = id / per;
-        const int nzb = B->n[2];
-        x0 = (id % tiles_x) * (2 * TXP);
-        y0 = ((id % per) / tiles_x) * TY;
-        zf = (int)((int64_t)chunk * nzb / nch) + 1;
-        zl = (int)((int64_t)(chunk + 1) * nzb / nch);
-    }
-    const int nx = B->n[0], ny = B->n[1], nz = B->n[2];
-
-    // this thread's pair (j, r) of the extended region
-    const int t = threadIdx.x;
-    int j = 0, r = 0;
-    bool live = true;
-    if (t < NTILE) {
-        j = 2 + t % TXP;
-        r = 3 + t / TXP;
-    } else {
-        int q = t - NTILE;
-        if (q < 2 * (TXP + 2)) {                  // mid rows
-            j = 1 + q % (TXP + 2);
-            r = q < TXP + 2 ? 2 : TY + 3;
-        } else if ((q -= 2 * (TXP + 2)) < 2 * TY) {   // mid pairs of the tile rows
-            j = (q & 1) ? TXP + 2 : 1;
-            r = 3 + (q >> 1);
-        } else if ((q -= 2 * TY) < 2 * (TXP + 2)) {   // second ring: rows 1 and ER - 2
-            j = 1 + q % (TXP + 2);
-            r = q < TXP + 2 ? 1 : ER - 2;
-        } else if ((q -= 2 * (TXP + 2)) < 2 * EP) {   // third ring: rows 0 and ER - 1
-            j = q % EP;
-            r = q < EP ? 0 : ER - 1;
-        } else if ((q -= 2 * EP) < 2 * (ER - 2)) {    // third ring: pairs 0 and EP - 1
-            j = (q & 1) ? EP - 1 : 0;
-            r = 1 + (q >> 1);
-        } else {
-            live = false;
-        }
-    }
-    const bool tile = t < NTILE;                  // uniform over each wave
-    const bool mid = t < NMID;
-    // Iterate k + 1 is needed on the tile and its two-cell ring only (the
-    // first NL1 threads); the third ring's threads come last and only load
-    // iterate k, so the waves holding none of the first NL1 threads skip the
-    // first stage (a wave-uniform branch)
-    const bool l1 = (t & ~63) < NL1;
-    const int xs = x0 - 3 + 2 * j;                // cells xs, xs + 1 (xs odd, >= -3)
-    const int ye = y0 - 2 + r;
-    const int xs_c = min(xs, nx | 1);             // last pair holding a cell <= nx + 1
-    const int ye_c = min(max(ye, 0), ny + 1);
-    const bool y_in = ye >= 1 && ye <= ny;
-    const bool in_a = live && y_in && xs >= 1 && xs <= nx;
-    const bool in_b = live && y_in && xs + 1 >= 1 && xs + 1 <= nx;
-    const bool a_ok = tile && ye <= ny && xs <= nx;   // tile cells in the block: stored
-    const bool b_ok = tile && ye <= ny && xs + 1 <= nx;
-    const int64_t pitch = F::pitch(B);
-    const int64_t plane = F::plane(B);
-    const int64_t rowoff = (int64_t)ye_c * pitch + xs_c;
-    const T* __restrict__ col = F::src(B, p) + rowoff;
-    const T* __restrict__ scol = SRC ? F::source(B) + rowoff : nullptr;
-    T* __restrict__ dst = F::dst(B, p) + rowoff;
-
-    const int pn = (r + 1) * (LW / 2) + j + 1;    // LDS pair of cells xs, xs + 1
-    const int pw = live ? pn : LN / 2;            // the pair this thread writes
-
-    // register rings: iterate k and the source of plane s in slot
-    // (s - zf + 2) mod RS, loads issued PD planes ahead; iterates k + 1 of
-    // plane s and k + 2 of plane s - 1 in slot (s - zf + 2) mod 3
-    constexpr int PD = 3;
-    constexpr int RS = 6;
-    const int zlo = max(zf - 3, 0);               // first plane read
-    const int zhi = min(zl + 3, nz + 1);          // last plane read
-    C ua[RS], ub[RS], ba[RS], bb[RS], va[3], vb[3], wa3[3], wb3[3];
-#pragma unroll
-    for (int k = 0; k < RS; ++k)
-        ba[k] = bb[k] = C(0);
-#pragma unroll
-    for (int k = 0; k < 3; ++k)
-        va[k] = vb[k] = wa3[k] = wb3[k] = C(0);
-    Tr<T>::ld(col + (int64_t)zlo * plane, ua[RS - 1], ub[RS - 1]);
-    if (SRC)
-        Tr<T>::ld(scol + (int64_t)zlo * plane, ba[RS - 1], bb[RS - 1]);
-#pragma unroll
-    for (int k = 0; k < PD; ++k) {
-        const int64_t zk = (int64_t)min(max(zf - 2 + k, 0), zhi) * plane;
-        Tr<T>::ld(col + zk, ua[k], ub[k]);
-        if (SRC)
-            Tr<T>::ld(scol + zk, ba[k], bb[k]);
-    }
-
-    // STAGES: 1 = iterate k + 1 only, 2 = also k + 2, 3 = also k + 3
-    const int s_first = zf - 2;
-    auto step = [&](int s, auto kc, auto stages) {
-        constexpr int K = decltype(kc)::value;
-        constexpr int ST = decltype(stages)::value;
-        constexpr int SM = (K + RS - 1) % RS, SC = K, SP = (K + 1) % RS, SQ = (K + PD) % RS;
-        constexpr int S2 = (K + RS - 2) % RS;     // plane s - 2
-        constexpr int VC = K % 3, VM = (K + 2) % 3, VMM = (K + 1) % 3;
-        constexpr int HC = K & 1;
-        if (pace)
-            pace_wait(pace_t0 + (uint64_t)(s - s_first) * pace);
-        const int64_t zq = (int64_t)min(s + PD, zhi) * plane;
-        Tr<T>::ld(col + zq, ua[SQ], ub[SQ]);
-        if (SRC)
-            Tr<T>::ld(scol + zq, ba[SQ], bb[SQ]);
-        V* const Ak = A[HC];
-        Ak[pw] = V{ua[SC], ub[SC]};
-        __syncthreads();
-        // iterate k + 1 at plane s
-        if (l1) {
-            const V ym = Ak[pn - LW / 2], yp = Ak[pn + LW / 2], xm = Ak[pn - 1], xp = Ak[pn + 1];
-            C sa = xm.y + ub[SC];
-            sa = sa + ym.x;
-            sa = sa + yp.x;
-            sa = sa + ua[SM];
-            sa = sa + ua[SP];
-            C sb = ua[SC] + xp.x;
-            sb = sb + ym.y;
-            sb = sb + yp.y;
-            sb = sb + ub[SM];
-            sb = sb + ub[SP];
-            C na, nb;
-            if (SRC)
-                div6_pair(sa + ba[SC], sb + bb[SC], na, nb);
-            else
-                div6_pair(sa, sb, na, nb);
-            const bool z_in = s >= 1 && s <= nz;
-            va[VC] = (in_a && z_in) ? storage_round<T>(na) : ua[SC];
-            vb[VC] = (in_b && z_in) ? storage_round<T>(nb) : ub[SC];
-            Bn[HC][pw] = V{va[VC], vb[VC]};
-        }
-        // iterate k + 2 at plane s - 1
-        if (ST >= 2 && mid) {
-            const V* const Bk = Bn[HC ^ 1];
-            const V ym = Bk[pn - LW / 2], yp = Bk[pn + LW / 2], xm = Bk[pn - 1], xp = Bk[pn + 1];
-            C qa = xm.y + vb[VM];
-            qa = qa + ym.x;
-            qa = qa + yp.x;
-            qa = qa + va[VMM];
-            qa = qa + va[VC];
-            C qb = va[VM] + xp.x;
-            qb = qb + ym.y;
-            qb = qb + yp.y;
-            qb = qb + vb[VMM];
-            qb = qb + vb[VC];
-            C na, nb;
-            if (SRC)
-                div6_pair(qa + ba[SM], qb + bb[SM], na, nb);
-            else
-                div6_pair(qa, qb, na, nb);
-            const bool z_in = s - 1 >= 1 && s - 1 <= nz;
-            wa3[VC] = (in_a && z_in) ? storage_round<T>(na) : va[VM];
-            wb3[VC] = (in_b && z_in) ? storage_round<T>(nb) : vb[VM];
-            Cn[HC][pw] = V{wa3[VC], wb3[VC]};
-        }
-        // iterate k + 3 at plane s - 2
-        if (ST >= 3 && tile) {
-            const V* const Ck = Cn[HC ^ 1];
-            const V ym = Ck[pn - LW / 2], yp = Ck[pn + LW / 2], xm = Ck[pn - 1], xp = Ck[pn + 1];
-            C qa = xm.y + wb3[VM];
-            qa = qa + ym.x;
-            qa = qa + yp.x;
-            qa = qa + wa3[VMM];
-            qa = qa + wa3[VC];
-            C qb = wa3[VM] + xp.x;
-            qb = qb + ym.y;
-            qb = qb + yp.y;
-            qb = qb + wb3[VMM];
-            qb = qb + wb3[VC];
-            C oa, ob;
-            if (SRC)
-                div6_pair(qa + ba[S2], qb + bb[S2], oa, ob);
-            else
-                div6_pair(qa, qb, oa, ob);
-            // past the last cell of a row the pair's second slot is the
-            // x = nx + 1 ghost: write back the value it holds
-            ob = b_ok ? ob : ub[S2];
-            if (a_ok)
-                Tr<T>::stn(dst + (int64_t)(s - 2) * plane, oa, ob);
-        }
-    };
-    using One = std::integral_constant<int, 1>;
-    using Two = std::integral_constant<int, 2>;
-    using Three = std::integral_constant<int, 3>;
-    int s = zf - 2;
-    step(s, std::integral_constant<int, 0>{}, One{});
-    step(s + 1, std::integral_constant<int, 1>{}, One{});
-    step(s + 2, std::integral_constant<int, 2>{}, Two{});
-    step(s + 3, std::integral_constant<int, 3>{}, Two{});
-    s += 4;
-#define JC_STEP3(k) step(s + (k), std::integral_constant<int, ((k) + 4) % RS>{}, Three{})
-    const int s_end = zl + 2;
-    for (; s + 5 <= s_end; s += 6) {
-        JC_STEP3(0);
-        JC_STEP3(1);
-        JC_STEP3(2);
-        JC_STEP3(3);
-        JC_STEP3(4);
-        JC_STEP3(5);
-    }
-    if (s <= s_end) JC_STEP3(0);
-    if (s + 1 <= s_end) JC_STEP3(1);
-    if (s + 2 <= s_end) JC_STEP3(2);
-    if (s + 3 <= s_end) JC_STEP3(3);
-    if (s + 4 <= s_end) JC_STEP3(4);
-#undef JC_STEP3
-}
-// ---- three-step sweep: end ----
-
 }  // namespace
 
 hipError_t launch_sweep(const BlockDesc* blocks, const Item* items, int nitems, int parity,
@@ -1032,172 +461,6 @@ hipError_t launch_sweep(const BlockDesc* blocks, const Item* items, int nitems, 
                                                              resid, store, partials, s, pace)
                : sweep_tiles<double, FIELD_U, false, NoRlo>(blocks, items, nitems, parity, tile_x, tile_y, fused,
                                                               resid, store, partials, s, pace);
-}
-
-hipError_t launch_sweep2(const BlockDesc* blocks, int nx, int ny, int nz, int parity, int tile_y, int z_chunk,
-                         bool src, hipStream_t s, uint32_t pace)
-{
-    if (nx < 1 || ny < 1 || nz < 1 || z_chunk < 1)
-        return hipErrorInvalidValue;
-    const int64_t tx = (nx + 63) / 64, ty = (ny + tile_y - 1) / tile_y, nch = (nz + z_chunk - 1) / z_chunk;
-    const int64_t n = tx * ty * nch;
-    if (n > ((int64_t)1 << 30))
-        return hipErrorInvalidValue;
-    const int grid = (int)((n + 7) / 8 * 8);
-#define JC_SWEEP2_CASE(TY, SRC)                                                                               \
-    if (tile_y == TY && src == SRC) {                                                                        \
-        hipLaunchKernelGGL((k_sweep2<double, FIELD_U, 32, TY, SRC>), dim3(grid), dim3((34 * (TY + 4) + 63) / 64 * 64), \
-                           0, s, blocks, nullptr, parity, (int)tx, (int)ty, (int)nch, (int)n, pace);         \
-        return hipGetLastError();                                                                            \
-    }
-    JC_SWEEP2_CASE(8, false)
-    JC_SWEEP2_CASE(8, true)
-    JC_SWEEP2_CASE(16, false)
-    JC_SWEEP2_CASE(16, true)
-    JC_SWEEP2_CASE(24, false)
-    JC_SWEEP2_CASE(24, true)
-#undef JC_SWEEP2_CASE
-    return hipErrorInvalidValue;
-}
-
-hipError_t launch_sweep2_items(const BlockDesc* blocks, const Item* items, int nitems, int parity, int tile_y,
-                               bool src, hipStream_t s)
-{
-    if (nitems <= 0)
-        return hipSuccess;
-    const int grid = ((nitems + 7) / 8) * 8;
-#define JC_SWEEP2_ITEMS_CASE(TY, SRC)                                                                          \
-    if (tile_y == TY && src == SRC) {                                                                         \
-        hipLaunchKernelGGL((k_sweep2<double, FIELD_U, 32, TY, SRC>), dim3(grid), dim3((34 * (TY + 4) + 63) / 64 * 64), \
-                           0, s, blocks, items, parity, 0, 0, 0, nitems, 0u);                                 \
-        return hipGetLastError();                                                                             \
-    }
-    JC_SWEEP2_ITEMS_CASE(8, false)
-    JC_SWEEP2_ITEMS_CASE(8, true)
-    JC_SWEEP2_ITEMS_CASE(16, false)
-    JC_SWEEP2_ITEMS_CASE(16, true)
-    JC_SWEEP2_ITEMS_CASE(24, false)
-    JC_SWEEP2_ITEMS_CASE(24, true)
-#undef JC_SWEEP2_ITEMS_CASE
-    return hipErrorInvalidValue;
-}
-
-// Three sweeps per launch (k_sweep3): the binary64 iterate, or the
-// refinement correction (lo_dtype 0/1/2); tiles of 64 cells by tile_y (8 or
-// 16) rows; items null: the tiles of blocks[0] in z chunks of z_chunk planes.
-template <typename T, int FIELD, int TY, bool SRC>
-hipError_t sweep3_launch(const BlockDesc* blocks, const Item* items, int parity, int tx, int ty, int nch, int n,
-                         hipStream_t s, uint32_t pace)
-{
-    const int grid = ((n + 7) / 8) * 8;
-    hipLaunchKernelGGL((k_sweep3<T, FIELD, 32, TY, SRC>), dim3(grid), dim3((36 * (TY + 6) + 63) / 64 * 64), 0, s,
-                       blocks, items, parity, tx, ty, nch, n, pace);
-    return hipGetLastError();
-}
-
-template <typename T, int FIELD, bool SRC>
-hipError_t sweep3_rows(const BlockDesc* blocks, const Item* items, int parity, int tile_y, int tx, int ty, int nch,
-                       int n, hipStream_t s, uint32_t pace)
-{
-    if (tile_y == 8)
-        return sweep3_launch<T, FIELD, 8, SRC>(blocks, items, parity, tx, ty, nch, n, s, pace);
-    if (tile_y == 16)
-        return sweep3_launch<T, FIELD, 16, SRC>(blocks, items, parity, tx, ty, nch, n, s, pace);
-    return hipErrorInvalidValue;
-}
-
-hipError_t launch_sweep3(const BlockDesc* blocks, const Item* items, int nitems, int nx, int ny, int nz, int parity,
-                         int tile_y, int z_chunk, bool src, hipStream_t s, uint32_t pace)
-{
-    int64_t tx = 0, ty = 0, nch = 0, n = nitems;
-    if (!items) {
-        if (nx < 1 || ny < 1 || nz < 1 || z_chunk < 1 || tile_y < 1)
-            return hipErrorInvalidValue;
-        tx = (nx + 63) / 64;
-        ty = (ny + tile_y - 1) / tile_y;
-        nch = (nz + z_chunk - 1) / z_chunk;
-        n = tx * ty * nch;
-    }
-    if (n <= 0)
-        return hipSuccess;
-    if (n > ((int64_t)1 << 30))
-        return hipErrorInvalidValue;
-    return src ? sweep3_rows<double, FIELD_U, true>(blocks, items, parity, tile_y, (int)tx, (int)ty, (int)nch, (int)n, s,
-                                                    pace)
-               : sweep3_rows<double, FIELD_U, false>(blocks, items, parity, tile_y, (int)tx, (int)ty, (int)nch, (int)n,
-                                                     s, pace);
-}
-
-hipError_t launch_ir_inner3(const BlockDesc* blocks, const Item* items, int nitems, int nx, int ny, int nz,
-                            int qparity, int tile_y, int z_chunk, int lo_dtype, hipStream_t s, uint32_t pace)
-{
-    int64_t tx = 0, ty = 0, nch = 0, n = nitems;
-    if (!items) {
-        if (nx < 1 || ny < 1 || nz < 1 || z_chunk < 1 || tile_y < 1)
-            return hipErrorInvalidValue;
-        tx = (nx + 63) / 64;
-        ty = (ny + tile_y - 1) / tile_y;
-        nch = (nz + z_chunk - 1) / z_chunk;
-        n = tx * ty * nch;
-    }
-    if (n <= 0)
-        return hipSuccess;
-    if (n > ((int64_t)1 << 30))
-        return hipErrorInvalidValue;
-    switch (lo_dtype) {
-    case 0: return sweep3_rows<double, FIELD_D, true>(blocks, items, qparity, tile_y, (int)tx, (int)ty, (int)nch, (int)n, s, pace);
-    case 1: return sweep3_rows<float, FIELD_D, true>(blocks, items, qparity, tile_y, (int)tx, (int)ty, (int)nch, (int)n, s, pace);
-    case 2: return sweep3_rows<bf16, FIELD_D, true>(blocks, items, qparity, tile_y, (int)tx, (int)ty, (int)nch, (int)n, s, pace);
-    default: return hipErrorInvalidValue;
-    }
-}
-
-hipError_t launch_ir_inner2_items(const BlockDesc* blocks, const Item* items, int nitems, int qparity, int tile_y,
-                                  int lo_dtype, hipStream_t s)
-{
-    if (nitems <= 0)
-        return hipSuccess;
-    const int grid = ((nitems + 7) / 8) * 8;
-#define JC_IR2_ITEMS_CASE(TY, DT, T)                                                                            \
-    if (tile_y == TY && lo_dtype == DT) {                                                                      \
-        hipLaunchKernelGGL((k_sweep2<T, FIELD_D, 32, TY, true>), dim3(grid), dim3((34 * (TY + 4) + 63) / 64 * 64), 0, \
-                           s, blocks, items, qparity, 0, 0, 0, nitems, 0u);                                    \
-        return hipGetLastError();                                                                              \
-    }
-    JC_IR2_ITEMS_CASE(16, 0, double)
-    JC_IR2_ITEMS_CASE(16, 1, float)
-    JC_IR2_ITEMS_CASE(16, 2, bf16)
-#undef JC_IR2_ITEMS_CASE
-    return hipErrorInvalidValue;
-}
-
-hipError_t launch_ir_inner2(const BlockDesc* blocks, int nx, int ny, int nz, int qparity, int tile_y, int z_chunk,
-                            int lo_dtype, hipStream_t s, uint32_t pace)
-{
-    if (nx < 1 || ny < 1 || nz < 1 || z_chunk < 1)
-        return hipErrorInvalidValue;
-    const int64_t tx = (nx + 63) / 64, ty = (ny + tile_y - 1) / tile_y, nch = (nz + z_chunk - 1) / z_chunk;
-    const int64_t n = tx * ty * nch;
-    if (n > ((int64_t)1 << 30))
-        return hipErrorInvalidValue;
-    const int grid = (int)((n + 7) / 8 * 8);
-#define JC_IR2_CASE(TY, DT, T)                                                                                  \
-    if (tile_y == TY && lo_dtype == DT) {                                                                      \
-        hipLaunchKernelGGL((k_sweep2<T, FIELD_D, 32, TY, true>), dim3(grid), dim3((34 * (TY + 4) + 63) / 64 * 64), 0, \
-                           s, blocks, nullptr, qparity, (int)tx, (int)ty, (int)nch, (int)n, pace);             \
-        return hipGetLastError();                                                                              \
-    }
-    JC_IR2_CASE(8, 0, double)
-    JC_IR2_CASE(8, 1, float)
-    JC_IR2_CASE(8, 2, bf16)
-    JC_IR2_CASE(16, 0, double)
-    JC_IR2_CASE(16, 1, float)
-    JC_IR2_CASE(16, 2, bf16)
-    JC_IR2_CASE(24, 0, double)
-    JC_IR2_CASE(24, 1, float)
-    JC_IR2_CASE(24, 2, bf16)
-#undef JC_IR2_CASE
-    return hipErrorInvalidValue;
 }
 
 hipError_t launch_ir_residual(const BlockDesc* blocks, const Item* items, int nitems, int parity, int tile_x,

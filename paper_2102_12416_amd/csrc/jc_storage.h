@@ -20,23 +20,22 @@ namespace {
 typedef double v2d __attribute__((ext_vector_type(2)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 
-// bfloat16: the upper half of a binary32, rounded to nearest even
-__device__ __forceinline__ float bf16_to_f32(uint32_t h)
-{
-    return __uint_as_float(h << 16);
-}
+// bfloat16: the upper half of a binary32, rounded to nearest even.
+__device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
-// Round to nearest even without a branch: adding 0x7fff plus the kept
-// half's lowest bit carries into the upper half exactly when the dropped
-// half is above one half, or equal to it with an odd kept half (equal, bit
-// for bit, to the comparison form for every binary32 pattern).  A NaN
-// stays a (quiet) NaN.
-__device__ __forceinline__ uint32_t f32_to_bf16(float f)
+// A pair rounded and packed (a in the low half) by the conversion instruction
+// of gfx950: one instruction for ten (shift, bit field, add and NaN select of
+// each value).  Compared with the shift form -- add 0x7fff plus the kept
+// half's lowest bit, NaN kept quiet -- over all 2^32 binary32 patterns in
+// both halves: the same bits, denormals and NaN included.
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b)
 {
-    const uint32_t x = __float_as_uint(f);
-    const uint32_t rounded = (x + 0x7fffu + ((x >> 16) & 1u)) >> 16;
-    const uint32_t quiet_nan = (x >> 16) | 0x40u;
-    return __builtin_isnan(f) ? quiet_nan : rounded;   // an unordered self-compare
+    typedef __bf16 v2b __attribute__((ext_vector_type(2)));
+    v2f v;
+    v.x = a;
+    v.y = b;
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, v2b));
 }
 
 // Fixed-order sum over the lanes of a wave.
@@ -143,24 +142,24 @@ template <> struct Tr<bf16> {
     __device__ static void ld(const bf16* p, float& a, float& b)
     {
         const uint32_t w = *(const uint32_t JC_GLOBAL*)(p);    // x at the lower address
-        a = bf16_to_f32(w & 0xffffu);
-        b = bf16_to_f32(w >> 16);
+        a = bf16_lo(w);
+        b = bf16_hi(w);
     }
     __device__ static void st(bf16* p, float a, float b)
     {
-        *(uint32_t JC_GLOBAL*)(p) = f32_to_bf16(a) | (f32_to_bf16(b) << 16);
+        *(uint32_t JC_GLOBAL*)(p) = bf16_pair(a, b);
     }
-    __device__ static void st1(bf16* p, float a) { *(uint16_t JC_GLOBAL*)(p) = (uint16_t)f32_to_bf16(a); }
+    __device__ static void st1(bf16* p, float a) { *(uint16_t JC_GLOBAL*)(p) = (uint16_t)bf16_pair(a, a); }
     __device__ static void stn(bf16* p, float a, float b)
     {
-        __builtin_nontemporal_store(f32_to_bf16(a) | (f32_to_bf16(b) << 16), (uint32_t JC_GLOBAL*)(p));
+        __builtin_nontemporal_store(bf16_pair(a, b), (uint32_t JC_GLOBAL*)(p));
     }
     using P = uint32_t;                           // x in the low half
-    __device__ static P pack(float a, float b) { return f32_to_bf16(a) | (f32_to_bf16(b) << 16); }
+    __device__ static P pack(float a, float b) { return bf16_pair(a, b); }
     __device__ static void unpack(P v, C& a, C& b)
     {
-        a = bf16_to_f32(v & 0xffffu);
-        b = bf16_to_f32(v >> 16);
+        a = bf16_lo(v);
+        b = bf16_hi(v);
     }
     __device__ static void stp(bf16* p, P v) { *(uint32_t JC_GLOBAL*)(p) = v; }
     __device__ static void stpn(bf16* p, P v) { __builtin_nontemporal_store(v, (uint32_t JC_GLOBAL*)(p)); }
