@@ -406,9 +406,10 @@ int jc_set_tiles(jc_ctx* ctx, int tile_x, int tile_y, int z_chunk);
  * was created with temporal = 1. */
 int jc_set_temporal_tiles(jc_ctx* ctx, int rows, int z_chunk);
 /* out = {sweeps per launch (2 or 3; 0 without temporal blocking), rows,
- * planes per work-group} of the multi-sweep launch.  Until set (jc_set_temporal_tiles or jc_autotune), rows are
- * 16 and the planes the library's default for the grid; with a z_chunk
- * given at creation or by jc_set_tiles the planes follow it, at least 32,
+ * planes per work-group} of the multi-sweep launch.  Until set (jc_set_temporal_tiles or jc_autotune), the shape
+ * is the library's default for the grid (16 rows; 8 for three sweeps of a
+ * large bfloat16 correction); with a z_chunk given at creation or by
+ * jc_set_tiles it is 16 rows and the planes follow z_chunk, at least 32,
  * halved (down to 8) while a launch would have fewer than 1024
  * work-groups. */
 int jc_temporal_info(const jc_ctx* ctx, int64_t out[3]);

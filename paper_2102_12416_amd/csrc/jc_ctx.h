@@ -140,7 +140,7 @@ struct jc_ctx {
     // (t2_zc 0: the one-sweep z_chunk, at least kTwoStepMinZ)
     int t2_rows = jc_rt::kTwoStepRows;
     int t2_zc = 0;
-    bool t2_auto = false;           // t2_zc is default_multi_planes'
+    bool t2_auto = false;           // the shape is default_multi_shape's
     // pace of the one-sweep launches of the solve loop (jc_set_pace): ticks
     // of the 100 MHz constant clock per plane step; 0 = none
     uint32_t pace = 0;

@@ -226,38 +226,47 @@ void build_items(jc_ctx* c)
     }
 }
 
-// Default planes of the multi-sweep launch (temporal blocking; 16 rows).  A
-// work-group marches up a column of zc planes in zc + 2 (depth - 1) steps
-// after a prologue of about two; a launch takes as many rounds of work-groups
-// as the compute units divide them into, and costs rounds x steps.  Several
-// rounds cost 15 % more, since their work-groups drift apart in z and miss L2
-// on the halo rows they share.  A small grid gets columns of a plane or two,
-// a large one whole rounds of long columns.  Measured, three sweeps per launch
-// (before: 8 planes, or 32 and the one-sweep chunk on large grids): 64^3
-// 16 x 1 7.3 us a launch against 11.4, 200 x 180 x 160 16 x 32 32 against 47,
-// 256^3 16 x 64 61 against 83, 512^3 16 x 512 423 against 443, and jc_autotune's
-// own shapes at 512^3 and 512 x 768 x 1536.
-int default_multi_planes(const jc_ctx* c)
+// Default shape of the multi-sweep launch (temporal blocking): 16 rows, and
+// planes as follows.  A work-group marches up a column of zc planes in zc + 2
+// (depth - 1) steps after a prologue of about two; a launch takes as many
+// rounds of work-groups as the compute units divide them into, and costs
+// rounds x steps.  Several rounds cost 15 % more, since their work-groups
+// drift apart in z and miss L2 on the halo rows they share.  A small grid gets
+// columns of a plane or two, a large one whole rounds of long columns.
+// Measured, three sweeps per launch (before: 8 planes, or 32 and the one-sweep
+// chunk on large grids): 64^3 16 x 1 7.3 us a launch against 11.4, 200 x 180 x
+// 160 16 x 32 32 against 47, 256^3 16 x 64 61 against 83, 512^3 16 x 512 423
+// against 443, and jc_autotune's own shapes at 512^3 and 512 x 768 x 1536.
+//
+// The bfloat16 correction moves few bytes per instruction and is bound by
+// issue, so from 2^23 cells on several work-groups share a compute unit: two
+// of 16 rows (two sweeps per launch, 512^3: 16 x 256 177 us per sweep, 16 x 512
+// 207) or four of 8 rows (three, 512^3: 8 x 256 186, 16 x 512 199; 1024^3: 1.99
+// ms against 2.13).
+void default_multi_shape(jc_ctx* c)
 {
     const HostBlock& b = c->blocks[0];
+    const bool issue_bound = c->opt.ir_enable && c->opt.ir_dtype == JC_BF16 &&
+                             b.n[0] * b.n[1] * b.n[2] >= ((int64_t)1 << 23);
+    const int64_t slots = (int64_t)kComputeUnits * (!issue_bound ? 1 : c->depth() == 3 ? 4 : 2);
+    c->t2_rows = issue_bound && c->depth() == 3 ? 8 : kTwoStepRows;
     const int64_t nz = std::min<int64_t>(b.n[2], 1 << 20);
-    const int64_t tiles = (b.n[0] + 63) / 64 * ((b.n[1] + kTwoStepRows - 1) / kTwoStepRows);
+    const int64_t tiles = (b.n[0] + 63) / 64 * ((b.n[1] + c->t2_rows - 1) / c->t2_rows);
     double best = 0;
-    int64_t planes = nz;
     for (int64_t k = 1; k <= nz; ++k) {
         const int64_t zc = (nz + k - 1) / k;
         const int64_t n = tiles * ((nz + zc - 1) / zc);
         // short columns only while they are needed to fill one round
-        if (k > 1 && zc < kMinZChunk && n > kComputeUnits)
+        if (k > 1 && zc < kMinZChunk && n > slots)
             break;
-        const int64_t rounds = (n + kComputeUnits - 1) / kComputeUnits;
+        const int64_t rounds = (n + slots - 1) / slots;
         const double cost = (double)rounds * (double)(zc + 2 * c->depth()) * (rounds > 1 ? 1.15 : 1.0);
         if (best == 0 || cost < best) {
             best = cost;
-            planes = zc;
+            c->t2_zc = (int)zc;
         }
     }
-    return (int)planes;
+    c->t2_auto = true;
 }
 
 int validate_options(const jc_options* opt)
@@ -403,9 +412,8 @@ int build_geometry(jc_ctx* c, const int64_t grid[3], const std::vector<int64_t> 
     if (c->opt.tile_x <= 0 && c->opt.tile_y <= 0 && c->opt.z_chunk <= 0 && !c->opt.overlap)
         default_tiles(c, c->max_items, &c->tile_x, &c->tile_y, &c->z_chunk);
     build_items(c);
-    c->t2_auto = c->opt.temporal && c->opt.z_chunk <= 0;
-    if (c->t2_auto)
-        c->t2_zc = default_multi_planes(c);
+    if (c->opt.temporal && c->opt.z_chunk <= 0)
+        default_multi_shape(c);
     if (c->max_items > (int64_t)1 << 30)
         return fail(JC_ERR_INVALID, "work list too long");
     // arena layout
@@ -1755,6 +1763,7 @@ int jc_set_tiles(jc_ctx* c, int tile_x, int tile_y, int z_chunk)
     c->pace = 0;                           // a pace belongs to a shape
     if (c->t2_auto) {                      // the multi-sweep launch follows a z_chunk that was set
         c->t2_auto = false;
+        c->t2_rows = kTwoStepRows;
         c->t2_zc = 0;
     }
     build_items(c);
