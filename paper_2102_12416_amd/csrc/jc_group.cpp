@@ -190,11 +190,11 @@ int group_sweep3(jc_group* g)
     for (const Class& k : g->classes) {
         hipError_t e;
         if (!k.ir)
-            e = jc::launch_sweep3(g->d_desc(), g->d_items2() + k.item2_0, (int)k.items2.size(), 0, 0, 0, g->parity,
-                                  kGroupTwoStepRows, 0, k.src, g->stream);
+            e = jc::launch_sweep3_items(g->d_desc(), g->d_items2() + k.item2_0, (int)k.items2.size(), g->parity,
+                                        kGroupTwoStepRows, k.src, g->stream);
         else
-            e = jc::launch_ir_inner3(g->d_desc(), g->d_items2() + k.item2_0, (int)k.items2.size(), 0, 0, 0,
-                                     g->members[k.members[0]]->ir_q, kGroupTwoStepRows, 0, k.lo, g->stream);
+            e = jc::launch_ir_inner3_items(g->d_desc(), g->d_items2() + k.item2_0, (int)k.items2.size(),
+                                           g->members[k.members[0]]->ir_q, kGroupTwoStepRows, k.lo, g->stream);
         if (e != hipSuccess)
             return ghip(e, "group three-sweep launch");
     }

@@ -720,11 +720,23 @@ int two_step_chunk(const jc_ctx* c)
 // solve loop runs); the other launches run unpaced.
 uint32_t multi_pace(const jc_ctx* c, int depth) { return c->depth() == depth ? c->pace : 0u; }
 
+// The context's single block as a launch argument: the iterate, from copy p.
+jc::OneBlock one_block(const jc_ctx* c, int p)
+{
+    const BlockDesc& d = c->hdesc[0];
+    return {d.u[p], d.u[p ^ 1], d.b, d.plane, d.pitch, d.n[0], d.n[1], d.n[2], 0, 0, 0, 0};
+}
+
+// The same for the refinement correction.
+jc::OneBlock one_block_lo(const jc_ctx* c, int q)
+{
+    const BlockDesc& d = c->hdesc[0];
+    return {d.d[q], d.d[q ^ 1], d.rlo, d.lplane, d.lpitch, d.n[0], d.n[1], d.n[2], 0, 0, 0, 0};
+}
+
 hipError_t launch_two_step(jc_ctx* c, int rows, int zc, uint32_t pace)
 {
-    const HostBlock& b = c->blocks[0];
-    return jc::launch_sweep2(c->d_blocks(), (int)b.n[0], (int)b.n[1], (int)b.n[2], c->parity, rows, zc,
-                             c->opt.with_source != 0, c->stream, pace);
+    return jc::launch_sweep2(one_block(c, c->parity), rows, zc, c->opt.with_source != 0, c->stream, pace);
 }
 hipError_t launch_two_step(jc_ctx* c, int rows, int zc) { return launch_two_step(c, rows, zc, multi_pace(c, 2)); }
 
@@ -732,9 +744,7 @@ hipError_t launch_two_step(jc_ctx* c, int rows, int zc) { return launch_two_step
 // qparity -> qparity ^ 1).
 hipError_t launch_ir_two_step(jc_ctx* c, int qparity, int rows, int zc, uint32_t pace)
 {
-    const HostBlock& b = c->blocks[0];
-    return jc::launch_ir_inner2(c->d_blocks(), (int)b.n[0], (int)b.n[1], (int)b.n[2], qparity, rows, zc,
-                                c->opt.ir_dtype, c->stream, pace);
+    return jc::launch_ir_inner2(one_block_lo(c, qparity), rows, zc, c->opt.ir_dtype, c->stream, pace);
 }
 hipError_t launch_ir_two_step(jc_ctx* c, int qparity, int rows, int zc)
 {
@@ -744,17 +754,13 @@ hipError_t launch_ir_two_step(jc_ctx* c, int qparity, int rows, int zc)
 // Three sweeps in one launch (temporal blocking, three per launch).
 hipError_t launch_three_step(jc_ctx* c, int rows, int zc, uint32_t pace)
 {
-    const HostBlock& b = c->blocks[0];
-    return jc::launch_sweep3(c->d_blocks(), nullptr, 0, (int)b.n[0], (int)b.n[1], (int)b.n[2], c->parity, rows, zc,
-                             c->opt.with_source != 0, c->stream, pace);
+    return jc::launch_sweep3(one_block(c, c->parity), rows, zc, c->opt.with_source != 0, c->stream, pace);
 }
 hipError_t launch_three_step(jc_ctx* c, int rows, int zc) { return launch_three_step(c, rows, zc, multi_pace(c, 3)); }
 
 hipError_t launch_ir_three_step(jc_ctx* c, int qparity, int rows, int zc, uint32_t pace)
 {
-    const HostBlock& b = c->blocks[0];
-    return jc::launch_ir_inner3(c->d_blocks(), nullptr, 0, (int)b.n[0], (int)b.n[1], (int)b.n[2], qparity, rows, zc,
-                                c->opt.ir_dtype, c->stream, pace);
+    return jc::launch_ir_inner3(one_block_lo(c, qparity), rows, zc, c->opt.ir_dtype, c->stream, pace);
 }
 hipError_t launch_ir_three_step(jc_ctx* c, int qparity, int rows, int zc)
 {

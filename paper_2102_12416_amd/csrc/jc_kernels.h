@@ -22,11 +22,26 @@ hipError_t launch_sweep(const BlockDesc* blocks, const Item* items, int nitems, 
                         int tile_x, int tile_y, bool fused, bool resid, bool store, bool src, double* partials,
                         hipStream_t s, uint32_t pace = 0);
 
-// Two sweeps of the single block of a context without face pairs in one
-// launch (binary64): iterate k from copy parity, iterate k + 2 into copy
-// parity ^ 1.  Tiles of 64 cells by tile_y (8, 16 or 24) rows by z_chunk planes.
-hipError_t launch_sweep2(const BlockDesc* blocks, int nx, int ny, int nz, int parity, int tile_y, int z_chunk,
-                         bool src, hipStream_t s, uint32_t pace = 0);
+// The single block of a launch over one context, passed by value: the kernel
+// then starts from its arguments instead of a chain of table reads, each of
+// which misses the caches of a fresh launch (about half a microsecond of a
+// small grid's launch).  src / dst / source: element (0, 0, 0) of the
+// swept field's input and output copies and of its source, in its storage.
+// Work-groups: tiles_x x tiles_y tiles per z chunk; the first `rest` of the
+// chunks have `planes` + 1 planes, the others `planes`.
+struct OneBlock {
+    const void* src;
+    void* dst;
+    const void* source;
+    int64_t plane;
+    int32_t pitch, nx, ny, nz;
+    int32_t tiles_x, tiles_y, planes, rest;
+};
+
+// Two sweeps in one launch (k_sweep2), tiles of 64 cells by tile_y (8, 16 or
+// 24) rows by z_chunk planes of one block without face pairs: iterate k from
+// one.src, iterate k + 2 into one.dst.  The launch fills in the tiles.
+hipError_t launch_sweep2(OneBlock one, int tile_y, int z_chunk, bool src, hipStream_t s, uint32_t pace = 0);
 // The same over a work list of 64-cell by tile_y-row tiles of several
 // one-block contexts (groups): each item's block, its copy parity ^ flip.
 hipError_t launch_sweep2_items(const BlockDesc* blocks, const Item* items, int nitems, int parity, int tile_y,
@@ -34,22 +49,21 @@ hipError_t launch_sweep2_items(const BlockDesc* blocks, const Item* items, int n
 // The same for two inner sweeps of the refinement correction (copy
 // qparity -> qparity ^ 1, source r_lo; tile_y 8, 16 or 24): iterate k + 1 is
 // rounded to the storage format between the two sweeps.
-hipError_t launch_ir_inner2(const BlockDesc* blocks, int nx, int ny, int nz, int qparity, int tile_y, int z_chunk,
-                            int lo_dtype, hipStream_t s, uint32_t pace = 0);
+hipError_t launch_ir_inner2(OneBlock one, int tile_y, int z_chunk, int lo_dtype, hipStream_t s, uint32_t pace = 0);
 // The same over a work list of 64-cell by 16-row tiles (groups; each
 // item's flip must be 0: a refining member holds its iterate in copy 0).
 hipError_t launch_ir_inner2_items(const BlockDesc* blocks, const Item* items, int nitems, int qparity, int tile_y,
                                   int lo_dtype, hipStream_t s);
 
 // Three sweeps in one launch (k_sweep3), tiles of 64 cells by tile_y (8 or
-// 16) rows.  items null: the single block of blocks[0] (nx, ny, nz) in z
-// chunks of z_chunk planes; otherwise the work list items[0 .. nitems) of
-// such tiles (groups), each with its block and flip.
-hipError_t launch_sweep3(const BlockDesc* blocks, const Item* items, int nitems, int nx, int ny, int nz, int parity,
-                         int tile_y, int z_chunk, bool src, hipStream_t s, uint32_t pace = 0);
-// The same for the refinement correction (copy qparity -> qparity ^ 1).
-hipError_t launch_ir_inner3(const BlockDesc* blocks, const Item* items, int nitems, int nx, int ny, int nz,
-                            int qparity, int tile_y, int z_chunk, int lo_dtype, hipStream_t s, uint32_t pace = 0);
+// 16) rows; one block, or a work list of such tiles (groups).
+hipError_t launch_sweep3(OneBlock one, int tile_y, int z_chunk, bool src, hipStream_t s, uint32_t pace = 0);
+hipError_t launch_sweep3_items(const BlockDesc* blocks, const Item* items, int nitems, int parity, int tile_y,
+                               bool src, hipStream_t s);
+// The same for the refinement correction.
+hipError_t launch_ir_inner3(OneBlock one, int tile_y, int z_chunk, int lo_dtype, hipStream_t s, uint32_t pace = 0);
+hipError_t launch_ir_inner3_items(const BlockDesc* blocks, const Item* items, int nitems, int qparity, int tile_y,
+                                  int lo_dtype, hipStream_t s);
 
 // Many sweeps in one launch (k_resident): nsweeps Jacobi sweeps of blocks
 // that fit on chip (resident_fits), one work-group per block, iterate k from

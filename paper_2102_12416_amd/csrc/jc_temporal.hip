@@ -41,6 +41,16 @@ namespace {
 // by step parity.  Values at cells two steps out of the block (the
 // outermost ring of a tile on the block edge) are clamped loads that only
 // feed discarded results.
+//
+// Work: with items null, the ntiles tiles of `one` numbered from the
+// work-group index; otherwise the work list items[0 .. ntiles), whose tiles
+// must be 2 TXP cells by TY rows, each with its block and ping-pong flip
+// (groups).
+// The one block of a single context comes by value: a small launch is a
+// chain of latencies, and the table and 64-bit divisions it replaces were
+// part of it.  64^3, 16 rows, z chunks of 1, per sweep: two sweeps 2.64 ->
+// 2.40 us (2.86 -> 2.57 with a source), three 2.47 -> 2.33.
+
 // A pair of the arithmetic type rounded to the storage format and back:
 // iterate k + 1 is stored between the two sweeps of a one-sweep-per-launch
 // run, so the second sweep must read it at storage precision.
@@ -51,11 +61,6 @@ __device__ __forceinline__ void storage_round(typename Tr<T>::C& a, typename Tr<
         Tr<T>::unpack(Tr<T>::pack(a, b), a, b);
 }
 
-//
-// Work: with items null, the tiles of blocks[0] (tiles_x by tiles_y per z
-// chunk, nch chunks, ntiles in all) numbered from the work-group index;
-// otherwise the work list items[0 .. ntiles), whose tiles must be 2 TXP
-// cells by TY rows, each with its block and ping-pong flip (groups).
 // A pair of arithmetic values as one LDS access (16 bytes in binary64).
 template <typename C> struct Pair2;
 template <> struct Pair2<double> { using V = v2d; };
@@ -63,8 +68,8 @@ template <> struct Pair2<float> { using V = v2f; };
 
 template <typename T, int FIELD, int TXP, int TY, bool SRC>
 __global__ void __launch_bounds__(((TXP + 2) * (TY + 4) + 63) / 64 * 64)
-k_sweep2(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items, int parity, int tiles_x,
-         int tiles_y, int nch, int ntiles, uint32_t pace)
+k_sweep2(OneBlock one, const BlockDesc* __restrict__ blocks, const Item* __restrict__ items, int parity, int ntiles,
+         uint32_t pace)
 {
     using C = typename Tr<T>::C;
     using F = Fld<T, FIELD>;
@@ -85,26 +90,42 @@ k_sweep2(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items, i
     if (id >= ntiles)
         return;                                   // uniform over the work-group
     const uint64_t pace_t0 = pace ? __builtin_amdgcn_s_memrealtime() : 0;
-    const BlockDesc* B = blocks;
-    int p = parity, x0, y0, zf, zl;
+    const T *src, *source;
+    T* out;
+    int64_t pitch, plane;
+    int nx, ny, nz, x0, y0, zf, zl;
     if (items) {
         const Item it = items[id];
-        B = blocks + it.block;
-        p = parity ^ it.flip;
+        const BlockDesc* B = blocks + it.block;
+        const int p = parity ^ it.flip;
+        src = F::src(B, p);
+        out = F::dst(B, p);
+        source = F::source(B);
+        pitch = F::pitch(B);
+        plane = F::plane(B);
+        nx = B->n[0];
+        ny = B->n[1];
+        nz = B->n[2];
         x0 = it.x0;
         y0 = it.y0;
         zf = it.z0 + 1;
         zl = it.z0 + it.zlen;
     } else {
-        const int per = tiles_x * tiles_y;
-        const int chunk = id / per;
-        const int nzb = B->n[2];
-        x0 = (id % tiles_x) * (2 * TXP);
-        y0 = ((id % per) / tiles_x) * TY;
-        zf = (int)((int64_t)chunk * nzb / nch) + 1;
-        zl = (int)((int64_t)(chunk + 1) * nzb / nch);
+        src = static_cast<const T*>(one.src);
+        out = static_cast<T*>(one.dst);
+        source = static_cast<const T*>(one.source);
+        pitch = one.pitch;
+        plane = one.plane;
+        nx = one.nx;
+        ny = one.ny;
+        nz = one.nz;
+        const uint32_t row = (uint32_t)id / (uint32_t)one.tiles_x;
+        const int chunk = (int)(row / (uint32_t)one.tiles_y);
+        x0 = (int)((uint32_t)id - row * (uint32_t)one.tiles_x) * (2 * TXP);
+        y0 = ((int)row - chunk * one.tiles_y) * TY;
+        zf = chunk * one.planes + min(chunk, one.rest) + 1;
+        zl = zf + one.planes - (chunk < one.rest ? 0 : 1);
     }
-    const int nx = B->n[0], ny = B->n[1], nz = B->n[2];
 
     // this thread's pair (j, r) of the extended region
     const int t = threadIdx.x;
@@ -138,12 +159,10 @@ k_sweep2(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items, i
     const bool in_b = live && y_in && xs + 1 >= 1 && xs + 1 <= nx;
     const bool a_ok = tile && ye <= ny && xs <= nx;   // tile cells in the block: stored
     const bool b_ok = tile && ye <= ny && xs + 1 <= nx;
-    const int64_t pitch = F::pitch(B);
-    const int64_t plane = F::plane(B);
     const int64_t rowoff = (int64_t)ye_c * pitch + xs_c;
-    const T* __restrict__ col = F::src(B, p) + rowoff;
-    const T* __restrict__ scol = SRC ? F::source(B) + rowoff : nullptr;
-    T* __restrict__ dst = F::dst(B, p) + rowoff;
+    const T* __restrict__ col = src + rowoff;
+    const T* __restrict__ scol = SRC ? source + rowoff : nullptr;
+    T* __restrict__ dst = out + rowoff;
 
     const int pn = (r + 1) * (LW / 2) + j + 1;    // LDS pair of cells xs, xs + 1
     const int pw = live ? pn : LN / 2;            // the pair this thread writes
@@ -288,8 +307,8 @@ k_sweep2(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items, i
 // tiles of blocks[0]; else a work list of 2 TXP x TY tiles).
 template <typename T, int FIELD, int TXP, int TY, bool SRC>
 __global__ void __launch_bounds__(((TXP + 4) * (TY + 6) + 63) / 64 * 64)
-k_sweep3(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items, int parity, int tiles_x,
-         int tiles_y, int nch, int ntiles, uint32_t pace)
+k_sweep3(OneBlock one, const BlockDesc* __restrict__ blocks, const Item* __restrict__ items, int parity, int ntiles,
+         uint32_t pace)
 {
     using C = typename Tr<T>::C;
     using F = Fld<T, FIELD>;
@@ -313,26 +332,42 @@ k_sweep3(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items, i
     if (id >= ntiles)
         return;                                   // uniform over the work-group
     const uint64_t pace_t0 = pace ? __builtin_amdgcn_s_memrealtime() : 0;
-    const BlockDesc* B = blocks;
-    int p = parity, x0, y0, zf, zl;
+    const T *src, *source;
+    T* out;
+    int64_t pitch, plane;
+    int nx, ny, nz, x0, y0, zf, zl;
     if (items) {
         const Item it = items[id];
-        B = blocks + it.block;
-        p = parity ^ it.flip;
+        const BlockDesc* B = blocks + it.block;
+        const int p = parity ^ it.flip;
+        src = F::src(B, p);
+        out = F::dst(B, p);
+        source = F::source(B);
+        pitch = F::pitch(B);
+        plane = F::plane(B);
+        nx = B->n[0];
+        ny = B->n[1];
+        nz = B->n[2];
         x0 = it.x0;
         y0 = it.y0;
         zf = it.z0 + 1;
         zl = it.z0 + it.zlen;
     } else {
-        const int per = tiles_x * tiles_y;
-        const int chunk = id / per;
-        const int nzb = B->n[2];
-        x0 = (id % tiles_x) * (2 * TXP);
-        y0 = ((id % per) / tiles_x) * TY;
-        zf = (int)((int64_t)chunk * nzb / nch) + 1;
-        zl = (int)((int64_t)(chunk + 1) * nzb / nch);
+        src = static_cast<const T*>(one.src);
+        out = static_cast<T*>(one.dst);
+        source = static_cast<const T*>(one.source);
+        pitch = one.pitch;
+        plane = one.plane;
+        nx = one.nx;
+        ny = one.ny;
+        nz = one.nz;
+        const uint32_t row = (uint32_t)id / (uint32_t)one.tiles_x;
+        const int chunk = (int)(row / (uint32_t)one.tiles_y);
+        x0 = (int)((uint32_t)id - row * (uint32_t)one.tiles_x) * (2 * TXP);
+        y0 = ((int)row - chunk * one.tiles_y) * TY;
+        zf = chunk * one.planes + min(chunk, one.rest) + 1;
+        zl = zf + one.planes - (chunk < one.rest ? 0 : 1);
     }
-    const int nx = B->n[0], ny = B->n[1], nz = B->n[2];
 
     // this thread's pair (j, r) of the extended region
     const int t = threadIdx.x;
@@ -378,12 +413,10 @@ k_sweep3(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items, i
     const bool in_b = live && y_in && xs + 1 >= 1 && xs + 1 <= nx;
     const bool a_ok = tile && ye <= ny && xs <= nx;   // tile cells in the block: stored
     const bool b_ok = tile && ye <= ny && xs + 1 <= nx;
-    const int64_t pitch = F::pitch(B);
-    const int64_t plane = F::plane(B);
     const int64_t rowoff = (int64_t)ye_c * pitch + xs_c;
-    const T* __restrict__ col = F::src(B, p) + rowoff;
-    const T* __restrict__ scol = SRC ? F::source(B) + rowoff : nullptr;
-    T* __restrict__ dst = F::dst(B, p) + rowoff;
+    const T* __restrict__ col = src + rowoff;
+    const T* __restrict__ scol = SRC ? source + rowoff : nullptr;
+    T* __restrict__ dst = out + rowoff;
 
     const int pn = (r + 1) * (LW / 2) + j + 1;    // LDS pair of cells xs, xs + 1
     const int pw = live ? pn : LN / 2;            // the pair this thread writes
@@ -534,172 +567,127 @@ k_sweep3(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items, i
 }
 // ---- three-step sweep: end ----
 
-}  // namespace
-
-hipError_t launch_sweep2(const BlockDesc* blocks, int nx, int ny, int nz, int parity, int tile_y, int z_chunk,
-                         bool src, hipStream_t s, uint32_t pace)
+// Fills in the tiles of a launch over one block; the work-groups, or 0 where
+// there are too many.
+int one_block_tiles(OneBlock& one, int tile_y, int z_chunk)
 {
-    if (nx < 1 || ny < 1 || nz < 1 || z_chunk < 1)
-        return hipErrorInvalidValue;
-    const int64_t tx = (nx + 63) / 64, ty = (ny + tile_y - 1) / tile_y, nch = (nz + z_chunk - 1) / z_chunk;
-    const int64_t n = tx * ty * nch;
+    if (one.nx < 1 || one.ny < 1 || one.nz < 1 || z_chunk < 1 || tile_y < 1)
+        return 0;
+    const int64_t tx = (one.nx + 63) / 64, ty = (one.ny + tile_y - 1) / tile_y;
+    const int64_t nch = (one.nz + (int64_t)z_chunk - 1) / z_chunk, n = tx * ty * nch;
     if (n > ((int64_t)1 << 30))
-        return hipErrorInvalidValue;
-    const int grid = (int)((n + 7) / 8 * 8);
-#define JC_SWEEP2_CASE(TY, SRC)                                                                               \
-    if (tile_y == TY && src == SRC) {                                                                        \
-        hipLaunchKernelGGL((k_sweep2<double, FIELD_U, 32, TY, SRC>), dim3(grid), dim3((34 * (TY + 4) + 63) / 64 * 64), \
-                           0, s, blocks, nullptr, parity, (int)tx, (int)ty, (int)nch, (int)n, pace);         \
-        return hipGetLastError();                                                                            \
-    }
-    JC_SWEEP2_CASE(8, false)
-    JC_SWEEP2_CASE(8, true)
-    JC_SWEEP2_CASE(16, false)
-    JC_SWEEP2_CASE(16, true)
-    JC_SWEEP2_CASE(24, false)
-    JC_SWEEP2_CASE(24, true)
-#undef JC_SWEEP2_CASE
-    return hipErrorInvalidValue;
+        return 0;
+    one.tiles_x = (int32_t)tx;
+    one.tiles_y = (int32_t)ty;
+    one.planes = (int32_t)(one.nz / nch);
+    one.rest = (int32_t)(one.nz % nch);
+    return (int)n;
 }
 
-hipError_t launch_sweep2_items(const BlockDesc* blocks, const Item* items, int nitems, int parity, int tile_y,
-                               bool src, hipStream_t s)
-{
-    if (nitems <= 0)
-        return hipSuccess;
-    const int grid = ((nitems + 7) / 8) * 8;
-#define JC_SWEEP2_ITEMS_CASE(TY, SRC)                                                                          \
-    if (tile_y == TY && src == SRC) {                                                                         \
-        hipLaunchKernelGGL((k_sweep2<double, FIELD_U, 32, TY, SRC>), dim3(grid), dim3((34 * (TY + 4) + 63) / 64 * 64), \
-                           0, s, blocks, items, parity, 0, 0, 0, nitems, 0u);                                 \
-        return hipGetLastError();                                                                             \
-    }
-    JC_SWEEP2_ITEMS_CASE(8, false)
-    JC_SWEEP2_ITEMS_CASE(8, true)
-    JC_SWEEP2_ITEMS_CASE(16, false)
-    JC_SWEEP2_ITEMS_CASE(16, true)
-    JC_SWEEP2_ITEMS_CASE(24, false)
-    JC_SWEEP2_ITEMS_CASE(24, true)
-#undef JC_SWEEP2_ITEMS_CASE
-    return hipErrorInvalidValue;
-}
-
-// Three sweeps per launch (k_sweep3): the binary64 iterate, or the
-// refinement correction (lo_dtype 0/1/2); tiles of 64 cells by tile_y (8 or
-// 16) rows; items null: the tiles of blocks[0] in z chunks of z_chunk planes.
 template <typename T, int FIELD, int TY, bool SRC>
-hipError_t sweep3_launch(const BlockDesc* blocks, const Item* items, int parity, int tx, int ty, int nch, int n,
-                         hipStream_t s, uint32_t pace)
+hipError_t sweep2_launch(const OneBlock& one, const BlockDesc* blocks, const Item* items, int parity, int n, hipStream_t s,
+                         uint32_t pace)
 {
-    const int grid = ((n + 7) / 8) * 8;
-    hipLaunchKernelGGL((k_sweep3<T, FIELD, 32, TY, SRC>), dim3(grid), dim3((36 * (TY + 6) + 63) / 64 * 64), 0, s,
-                       blocks, items, parity, tx, ty, nch, n, pace);
+    const int grid = (n + 7) / 8 * 8;
+    hipLaunchKernelGGL((k_sweep2<T, FIELD, 32, TY, SRC>), dim3(grid), dim3((34 * (TY + 4) + 63) / 64 * 64), 0, s, one,
+                       blocks, items, parity, n, pace);
     return hipGetLastError();
 }
 
 template <typename T, int FIELD, bool SRC>
-hipError_t sweep3_rows(const BlockDesc* blocks, const Item* items, int parity, int tile_y, int tx, int ty, int nch,
-                       int n, hipStream_t s, uint32_t pace)
+hipError_t sweep2_rows(const OneBlock& one, const BlockDesc* blocks, const Item* items, int parity, int tile_y, int n,
+                       hipStream_t s, uint32_t pace)
 {
-    if (tile_y == 8)
-        return sweep3_launch<T, FIELD, 8, SRC>(blocks, items, parity, tx, ty, nch, n, s, pace);
-    if (tile_y == 16)
-        return sweep3_launch<T, FIELD, 16, SRC>(blocks, items, parity, tx, ty, nch, n, s, pace);
-    return hipErrorInvalidValue;
-}
-
-hipError_t launch_sweep3(const BlockDesc* blocks, const Item* items, int nitems, int nx, int ny, int nz, int parity,
-                         int tile_y, int z_chunk, bool src, hipStream_t s, uint32_t pace)
-{
-    int64_t tx = 0, ty = 0, nch = 0, n = nitems;
-    if (!items) {
-        if (nx < 1 || ny < 1 || nz < 1 || z_chunk < 1 || tile_y < 1)
-            return hipErrorInvalidValue;
-        tx = (nx + 63) / 64;
-        ty = (ny + tile_y - 1) / tile_y;
-        nch = (nz + z_chunk - 1) / z_chunk;
-        n = tx * ty * nch;
-    }
-    if (n <= 0)
-        return hipSuccess;
-    if (n > ((int64_t)1 << 30))
-        return hipErrorInvalidValue;
-    return src ? sweep3_rows<double, FIELD_U, true>(blocks, items, parity, tile_y, (int)tx, (int)ty, (int)nch, (int)n, s,
-                                                    pace)
-               : sweep3_rows<double, FIELD_U, false>(blocks, items, parity, tile_y, (int)tx, (int)ty, (int)nch, (int)n,
-                                                     s, pace);
-}
-
-hipError_t launch_ir_inner3(const BlockDesc* blocks, const Item* items, int nitems, int nx, int ny, int nz,
-                            int qparity, int tile_y, int z_chunk, int lo_dtype, hipStream_t s, uint32_t pace)
-{
-    int64_t tx = 0, ty = 0, nch = 0, n = nitems;
-    if (!items) {
-        if (nx < 1 || ny < 1 || nz < 1 || z_chunk < 1 || tile_y < 1)
-            return hipErrorInvalidValue;
-        tx = (nx + 63) / 64;
-        ty = (ny + tile_y - 1) / tile_y;
-        nch = (nz + z_chunk - 1) / z_chunk;
-        n = tx * ty * nch;
-    }
-    if (n <= 0)
-        return hipSuccess;
-    if (n > ((int64_t)1 << 30))
-        return hipErrorInvalidValue;
-    switch (lo_dtype) {
-    case 0: return sweep3_rows<double, FIELD_D, true>(blocks, items, qparity, tile_y, (int)tx, (int)ty, (int)nch, (int)n, s, pace);
-    case 1: return sweep3_rows<float, FIELD_D, true>(blocks, items, qparity, tile_y, (int)tx, (int)ty, (int)nch, (int)n, s, pace);
-    case 2: return sweep3_rows<bf16, FIELD_D, true>(blocks, items, qparity, tile_y, (int)tx, (int)ty, (int)nch, (int)n, s, pace);
+    switch (tile_y) {
+    case 8: return sweep2_launch<T, FIELD, 8, SRC>(one, blocks, items, parity, n, s, pace);
+    case 16: return sweep2_launch<T, FIELD, 16, SRC>(one, blocks, items, parity, n, s, pace);
+    case 24: return sweep2_launch<T, FIELD, 24, SRC>(one, blocks, items, parity, n, s, pace);
     default: return hipErrorInvalidValue;
     }
+}
+
+template <typename T, int FIELD, int TY, bool SRC>
+hipError_t sweep3_launch(const OneBlock& one, const BlockDesc* blocks, const Item* items, int parity, int n, hipStream_t s,
+                         uint32_t pace)
+{
+    const int grid = (n + 7) / 8 * 8;
+    hipLaunchKernelGGL((k_sweep3<T, FIELD, 32, TY, SRC>), dim3(grid), dim3((36 * (TY + 6) + 63) / 64 * 64), 0, s, one,
+                       blocks, items, parity, n, pace);
+    return hipGetLastError();
+}
+
+template <typename T, int FIELD, bool SRC>
+hipError_t sweep3_rows(const OneBlock& one, const BlockDesc* blocks, const Item* items, int parity, int tile_y, int n,
+                       hipStream_t s, uint32_t pace)
+{
+    switch (tile_y) {
+    case 8: return sweep3_launch<T, FIELD, 8, SRC>(one, blocks, items, parity, n, s, pace);
+    case 16: return sweep3_launch<T, FIELD, 16, SRC>(one, blocks, items, parity, n, s, pace);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+// The sweeps of the iterate (with or without a source) and of the correction
+// by storage format, `ROWS` = sweep2_rows or sweep3_rows.
+#define JC_FIELD_U(ROWS, one, blocks, items, parity, n, pace)                                                   \
+    (src ? ROWS<double, FIELD_U, true>(one, blocks, items, parity, tile_y, n, s, pace)                           \
+         : ROWS<double, FIELD_U, false>(one, blocks, items, parity, tile_y, n, s, pace))
+#define JC_FIELD_D(ROWS, one, blocks, items, parity, n, pace)                                                   \
+    (lo_dtype == 0   ? ROWS<double, FIELD_D, true>(one, blocks, items, parity, tile_y, n, s, pace)               \
+     : lo_dtype == 1 ? ROWS<float, FIELD_D, true>(one, blocks, items, parity, tile_y, n, s, pace)                \
+     : lo_dtype == 2 ? ROWS<bf16, FIELD_D, true>(one, blocks, items, parity, tile_y, n, s, pace)                 \
+                     : hipErrorInvalidValue)
+
+}  // namespace
+
+hipError_t launch_sweep2(OneBlock one, int tile_y, int z_chunk, bool src, hipStream_t s, uint32_t pace)
+{
+    const int n = one_block_tiles(one, tile_y, z_chunk);
+    return n < 1 ? hipErrorInvalidValue : JC_FIELD_U(sweep2_rows, one, nullptr, nullptr, 0, n, pace);
+}
+
+hipError_t launch_sweep3(OneBlock one, int tile_y, int z_chunk, bool src, hipStream_t s, uint32_t pace)
+{
+    const int n = one_block_tiles(one, tile_y, z_chunk);
+    return n < 1 ? hipErrorInvalidValue : JC_FIELD_U(sweep3_rows, one, nullptr, nullptr, 0, n, pace);
+}
+
+hipError_t launch_ir_inner2(OneBlock one, int tile_y, int z_chunk, int lo_dtype, hipStream_t s, uint32_t pace)
+{
+    const int n = one_block_tiles(one, tile_y, z_chunk);
+    return n < 1 ? hipErrorInvalidValue : JC_FIELD_D(sweep2_rows, one, nullptr, nullptr, 0, n, pace);
+}
+
+hipError_t launch_ir_inner3(OneBlock one, int tile_y, int z_chunk, int lo_dtype, hipStream_t s, uint32_t pace)
+{
+    const int n = one_block_tiles(one, tile_y, z_chunk);
+    return n < 1 ? hipErrorInvalidValue : JC_FIELD_D(sweep3_rows, one, nullptr, nullptr, 0, n, pace);
+}
+
+hipError_t launch_sweep2_items(const BlockDesc* blocks, const Item* items, int nitems, int parity, int tile_y, bool src,
+                               hipStream_t s)
+{
+    return nitems <= 0 ? hipSuccess : JC_FIELD_U(sweep2_rows, OneBlock{}, blocks, items, parity, nitems, 0u);
+}
+
+hipError_t launch_sweep3_items(const BlockDesc* blocks, const Item* items, int nitems, int parity, int tile_y, bool src,
+                               hipStream_t s)
+{
+    return nitems <= 0 ? hipSuccess : JC_FIELD_U(sweep3_rows, OneBlock{}, blocks, items, parity, nitems, 0u);
 }
 
 hipError_t launch_ir_inner2_items(const BlockDesc* blocks, const Item* items, int nitems, int qparity, int tile_y,
                                   int lo_dtype, hipStream_t s)
 {
-    if (nitems <= 0)
-        return hipSuccess;
-    const int grid = ((nitems + 7) / 8) * 8;
-#define JC_IR2_ITEMS_CASE(TY, DT, T)                                                                            \
-    if (tile_y == TY && lo_dtype == DT) {                                                                      \
-        hipLaunchKernelGGL((k_sweep2<T, FIELD_D, 32, TY, true>), dim3(grid), dim3((34 * (TY + 4) + 63) / 64 * 64), 0, \
-                           s, blocks, items, qparity, 0, 0, 0, nitems, 0u);                                    \
-        return hipGetLastError();                                                                              \
-    }
-    JC_IR2_ITEMS_CASE(16, 0, double)
-    JC_IR2_ITEMS_CASE(16, 1, float)
-    JC_IR2_ITEMS_CASE(16, 2, bf16)
-#undef JC_IR2_ITEMS_CASE
-    return hipErrorInvalidValue;
+    return nitems <= 0 ? hipSuccess : JC_FIELD_D(sweep2_rows, OneBlock{}, blocks, items, qparity, nitems, 0u);
 }
 
-hipError_t launch_ir_inner2(const BlockDesc* blocks, int nx, int ny, int nz, int qparity, int tile_y, int z_chunk,
-                            int lo_dtype, hipStream_t s, uint32_t pace)
+hipError_t launch_ir_inner3_items(const BlockDesc* blocks, const Item* items, int nitems, int qparity, int tile_y,
+                                  int lo_dtype, hipStream_t s)
 {
-    if (nx < 1 || ny < 1 || nz < 1 || z_chunk < 1)
-        return hipErrorInvalidValue;
-    const int64_t tx = (nx + 63) / 64, ty = (ny + tile_y - 1) / tile_y, nch = (nz + z_chunk - 1) / z_chunk;
-    const int64_t n = tx * ty * nch;
-    if (n > ((int64_t)1 << 30))
-        return hipErrorInvalidValue;
-    const int grid = (int)((n + 7) / 8 * 8);
-#define JC_IR2_CASE(TY, DT, T)                                                                                  \
-    if (tile_y == TY && lo_dtype == DT) {                                                                      \
-        hipLaunchKernelGGL((k_sweep2<T, FIELD_D, 32, TY, true>), dim3(grid), dim3((34 * (TY + 4) + 63) / 64 * 64), 0, \
-                           s, blocks, nullptr, qparity, (int)tx, (int)ty, (int)nch, (int)n, pace);             \
-        return hipGetLastError();                                                                              \
-    }
-    JC_IR2_CASE(8, 0, double)
-    JC_IR2_CASE(8, 1, float)
-    JC_IR2_CASE(8, 2, bf16)
-    JC_IR2_CASE(16, 0, double)
-    JC_IR2_CASE(16, 1, float)
-    JC_IR2_CASE(16, 2, bf16)
-    JC_IR2_CASE(24, 0, double)
-    JC_IR2_CASE(24, 1, float)
-    JC_IR2_CASE(24, 2, bf16)
-#undef JC_IR2_CASE
-    return hipErrorInvalidValue;
+    return nitems <= 0 ? hipSuccess : JC_FIELD_D(sweep3_rows, OneBlock{}, blocks, items, qparity, nitems, 0u);
 }
+#undef JC_FIELD_U
+#undef JC_FIELD_D
 
 }  // namespace jc
