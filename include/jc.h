@@ -285,7 +285,9 @@ int jc_solve_ir(jc_ctx* ctx, int inner_sweeps, double rtol, int64_t max_inner,
  * flags: bit 0 = capture jc_group_iterate windows as HIP graphs (needs a
  * non-null stream); bit 1 = two sweeps of every member per launch
  * (temporal blocking; every member one block, else JC_ERR_INVALID; tiles
- * of 64 cells x 16 rows x max(planes, 32); the first inner sweep of a
+ * of 64 cells x 16 rows x max(planes, 32) with a tile given, else of planes
+ * (and, for three binary32 or bfloat16 sweeps, cells x rows) that suit the
+ * members' sizes; the first inner sweep of a
  * refinement step and the last of an odd count are single-sweep launches;
  * results bitwise the same as one sweep per launch); bit 2 = three sweeps
  * per launch (the same conditions and tiles; a count that is not a

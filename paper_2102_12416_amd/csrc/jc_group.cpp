@@ -37,8 +37,9 @@ struct Class {
     int64_t max_rows = 1, max_nx = 1;    // largest ny * nz and nx of the class's blocks
     size_t item0 = 0;                // first joint item
     std::vector<Item> items;
-    size_t item2_0 = 0;              // first joint two-sweep item
-    std::vector<Item> items2;        // two-sweep tiles (groups that sweep twice per launch)
+    size_t item2_0 = 0;              // first joint multi-sweep item
+    std::vector<Item> items2;        // multi-sweep tiles (groups that sweep two or three times per launch)
+    int multi[3] = {64, 16, jc_rt::kTwoStepMinZ};    // their cells, rows and planes
     std::vector<int> members;
     // resident sweeps: one item per member, the largest blocks first, so
     // that the last work-groups to start are the shortest
@@ -46,10 +47,6 @@ struct Class {
     size_t itemr0 = 0;                             // first joint resident item
     jc::ResidentShape shape;                       // of the members' blocks
 };
-
-// Two-sweep tiles of a group: 64 cells by kGroupTwoStepRows rows, and at
-// least kTwoStepMinZ planes (the group's own z chunk if larger).
-constexpr int kGroupTwoStepRows = 16;
 
 }  // namespace
 
@@ -61,7 +58,7 @@ struct jc_group {
     std::vector<Class> classes;
     std::vector<BlockDesc> desc;        // joint block table, class-major
     std::vector<Item> items;            // joint work list, class-major
-    std::vector<Item> items2;           // joint two-sweep work list, class-major
+    std::vector<Item> items2;           // joint multi-sweep work list, class-major
     bool two_step = false;              // every launch sweeps every member twice (or three times)
     bool three_step = false;            // three sweeps of every member per launch
     bool resident = false;              // every window one launch, one work-group per member
@@ -137,6 +134,99 @@ int prime_faces(jc_group* g)
     return JC_OK;
 }
 
+// Multi-sweep tiles of a class: 64 cells by 16 rows, and planes as follows.
+// As in a launch over one context, a work-group marches a column of zc planes
+// in about zc + 2 depth steps and a launch takes as many rounds of them as the
+// compute units divide its columns into, so the planes are taken that minimise
+// rounds x steps; columns below 16 planes only while one round holds all.
+// Three sweeps of a binary32 or bfloat16 correction have tiles of 32 cells by
+// 32 rows to choose from as well (as many threads and as much LDS): members a
+// few tens of cells wide then waste less of a row.  The same tile costs 20 %
+// more a step in binary64, and 20 % with two sweeps, which takes the gain away.
+// Measured per launch (before: 64 x 16 x 32 throughout), members of four sizes
+// from the edge to half of it, with a source: 12 of edge 64, binary64 30 -> 15
+// us, binary32 31 -> 13; 56 of edge 32 28 -> 16 and 31 -> 11; 24 of edge 96 75
+// (as before) and 62 -> 49; 48 of edge 96 in bfloat16 118 -> 77.
+//
+// A given tile keeps 64 x 16 cells by its z chunk, at least kTwoStepMinZ; so
+// does a class of more than kMultiSearchItems such tiles, whose rounds are many
+// and hardly depend on the planes.
+constexpr int64_t kMultiSearchItems = 1 << 14;
+
+// Columns of `planes` planes of a class's members, and the longest of them.
+int64_t multi_count(const jc_group* g, const Class& k, int cells, int rows, int64_t planes, int64_t* longest)
+{
+    int64_t count = 0;
+    *longest = 0;
+    for (int m : k.members) {
+        const int64_t* n = g->members[m]->blocks[0].n;
+        const int64_t nch = (n[2] + planes - 1) / planes;
+        count += (n[0] + cells - 1) / cells * ((n[1] + rows - 1) / rows) * nch;
+        *longest = std::max(*longest, (n[2] + nch - 1) / nch);
+    }
+    return count;
+}
+
+void multi_shape(const jc_group* g, Class& k)
+{
+    const int depth = g->three_step ? 3 : 2;
+    int64_t longest = 0;
+    if (multi_count(g, k, 64, 16, jc_rt::kTwoStepMinZ, &longest) > kMultiSearchItems)
+        return;
+    int64_t best = 0;
+    const int shapes[2][2] = {{64, 16}, {32, 32}};
+    // a search of tens of microseconds at a hundred members
+    const int depths[] = {64, 48, 40, 32, 28, 24, 20, 16, 12, 10, 8, 6, 4, 3, 2, 1};
+    for (int i = 0; i < (depth == 3 && k.ir && k.lo != JC_F64 ? 2 : 1); ++i)
+        for (int planes : depths) {
+            const int64_t n = multi_count(g, k, shapes[i][0], shapes[i][1], planes, &longest);
+            if (planes < jc_rt::kMinZChunk && n > jc_rt::kComputeUnits)
+                break;
+            const int64_t rounds = (n + jc_rt::kComputeUnits - 1) / jc_rt::kComputeUnits;
+            const int64_t cost = rounds * (longest + 2 * depth);
+            if (best == 0 || cost < best) {
+                best = cost;
+                k.multi[0] = shapes[i][0];
+                k.multi[1] = shapes[i][1];
+                k.multi[2] = planes;
+            }
+        }
+}
+
+// The multi-sweep work list; search: each class's own shape.
+void multi_items(jc_group* g, bool search)
+{
+    g->items2.clear();
+    if (!g->two_step)
+        return;
+    for (Class& k : g->classes) {
+        k.multi[0] = 64;
+        k.multi[1] = 16;
+        k.multi[2] = std::max(g->tile[2], jc_rt::kTwoStepMinZ);
+        if (search)
+            multi_shape(g, k);
+        k.items2.clear();
+        for (int m : k.members)
+            member_items(g->members[m], k.multi, g->member_bstart[m], m, k.items2);
+        k.item2_0 = g->items2.size();
+        g->items2.insert(g->items2.end(), k.items2.begin(), k.items2.end());
+    }
+}
+
+// Offsets of the tables in the scratch, and its size.
+void group_layout(jc_group* g)
+{
+    size_t off = 0;
+    g->off_desc = off; off = align_up(off + sizeof(BlockDesc) * g->desc.size(), kAlign);
+    g->off_items = off; off = align_up(off + sizeof(Item) * g->items.size(), kAlign);
+    g->off_items2 = off; off = align_up(off + sizeof(Item) * std::max<size_t>(1, g->items2.size()), kAlign);
+    g->off_itemsr = off; off = align_up(off + sizeof(Item) * std::max<size_t>(1, g->itemsr.size()), kAlign);
+    g->off_partials = off; off = align_up(off + sizeof(double) * g->items.size(), kAlign);
+    g->off_lohi = off; off = align_up(off + sizeof(int32_t) * g->lohi.size(), kAlign);
+    g->off_out = off; off = align_up(off + sizeof(double) * g->members.size(), kAlign);
+    g->footprint = off;
+}
+
 // One sweep of every member.
 int group_sweep(jc_group* g)
 {
@@ -173,28 +263,27 @@ int group_sweep2(jc_group* g)
         hipError_t e;
         if (!k.ir)
             e = jc::launch_sweep2_items(g->d_desc(), g->d_items2() + k.item2_0, (int)k.items2.size(), g->parity,
-                                        kGroupTwoStepRows, k.src, g->stream);
+                                        k.multi[1], k.src, g->stream);
         else
             e = jc::launch_ir_inner2_items(g->d_desc(), g->d_items2() + k.item2_0, (int)k.items2.size(),
-                                           g->members[k.members[0]]->ir_q, kGroupTwoStepRows, k.lo, g->stream);
+                                           g->members[k.members[0]]->ir_q, k.multi[1], k.lo, g->stream);
         if (e != hipSuccess)
             return ghip(e, "group two-sweep launch");
     }
     return JC_OK;
 }
 
-// Three sweeps of every member in one launch per class (the two-sweep
-// tiles serve the three-sweep kernel too: 64 cells by 16 rows).
+// Three sweeps of every member in one launch per class.
 int group_sweep3(jc_group* g)
 {
     for (const Class& k : g->classes) {
         hipError_t e;
         if (!k.ir)
             e = jc::launch_sweep3_items(g->d_desc(), g->d_items2() + k.item2_0, (int)k.items2.size(), g->parity,
-                                        kGroupTwoStepRows, k.src, g->stream);
+                                        k.multi[1], k.src, g->stream);
         else
             e = jc::launch_ir_inner3_items(g->d_desc(), g->d_items2() + k.item2_0, (int)k.items2.size(),
-                                           g->members[k.members[0]]->ir_q, kGroupTwoStepRows, k.lo, g->stream);
+                                           g->members[k.members[0]]->ir_q, k.multi[1], k.lo, g->stream);
         if (e != hipSuccess)
             return ghip(e, "group three-sweep launch");
     }
@@ -377,10 +466,6 @@ int jc_group_create(jc_ctx* const* ctxs, int n, void* hip_stream, int flags, con
             const size_t i0 = g->items.size();
             const size_t first = k.items.size();
             member_items(c, g->tile, (int)g->desc.size(), m, k.items);
-            if (g->two_step) {
-                const int t2[3] = {64, kGroupTwoStepRows, std::max(g->tile[2], jc_rt::kTwoStepMinZ)};
-                member_items(c, t2, (int)g->desc.size(), m, k.items2);
-            }
             if (g->resident) {
                 const int64_t* bn = c->blocks[0].n;
                 Item it{};
@@ -397,8 +482,6 @@ int jc_group_create(jc_ctx* const* ctxs, int n, void* hip_stream, int flags, con
             g->lohi[2 * m + 1] = (int32_t)g->items.size();
         }
         k.bend = (int)g->desc.size();
-        k.item2_0 = g->items2.size();
-        g->items2.insert(g->items2.end(), k.items2.begin(), k.items2.end());
         std::stable_sort(k.itemsr.begin(), k.itemsr.end(), [&](const Item& a, const Item& b) {
             const int32_t *p = g->desc[a.block].n, *q = g->desc[b.block].n;
             return (int64_t)p[0] * p[1] * p[2] > (int64_t)q[0] * q[1] * q[2];
@@ -406,19 +489,18 @@ int jc_group_create(jc_ctx* const* ctxs, int n, void* hip_stream, int flags, con
         k.itemr0 = g->itemsr.size();
         g->itemsr.insert(g->itemsr.end(), k.itemsr.begin(), k.itemsr.end());
     }
+    multi_items(g, tile == nullptr);
+    group_layout(g);
+    if (tile == nullptr && g->footprint > (size_t)JC_STATIC_SCRATCH_BYTES) {
+        // a group whose tables fill the static scratch keeps the list that
+        // has always fitted there
+        multi_items(g, false);
+        group_layout(g);
+    }
     if (g->desc.size() > 65535 || g->items.size() > ((size_t)1 << 30) || g->items2.size() > ((size_t)1 << 30)) {
         delete g;
         return fail(JC_ERR_INVALID, "group too large for one launch");
     }
-    size_t off = 0;
-    g->off_desc = off; off = align_up(off + sizeof(BlockDesc) * g->desc.size(), kAlign);
-    g->off_items = off; off = align_up(off + sizeof(Item) * g->items.size(), kAlign);
-    g->off_items2 = off; off = align_up(off + sizeof(Item) * std::max<size_t>(1, g->items2.size()), kAlign);
-    g->off_itemsr = off; off = align_up(off + sizeof(Item) * std::max<size_t>(1, g->itemsr.size()), kAlign);
-    g->off_partials = off; off = align_up(off + sizeof(double) * g->items.size(), kAlign);
-    g->off_lohi = off; off = align_up(off + sizeof(int32_t) * g->lohi.size(), kAlign);
-    g->off_out = off; off = align_up(off + sizeof(double) * n, kAlign);
-    g->footprint = off;
     g->h_out_plain.assign(n, 0.0);
     *out = g;
     return JC_OK;

@@ -50,8 +50,9 @@ hipError_t launch_sweep2_items(const BlockDesc* blocks, const Item* items, int n
 // qparity -> qparity ^ 1, source r_lo; tile_y 8, 16 or 24): iterate k + 1 is
 // rounded to the storage format between the two sweeps.
 hipError_t launch_ir_inner2(OneBlock one, int tile_y, int z_chunk, int lo_dtype, hipStream_t s, uint32_t pace = 0);
-// The same over a work list of 64-cell by 16-row tiles (groups; each
-// item's flip must be 0: a refining member holds its iterate in copy 0).
+// The same over a work list of 64-cell by tile_y-row tiles, or of 32 cells by
+// 32 rows (tile_y 32) in binary32 and bfloat16 (groups; each item's flip must
+// be 0: a refining member holds its iterate in copy 0).
 hipError_t launch_ir_inner2_items(const BlockDesc* blocks, const Item* items, int nitems, int qparity, int tile_y,
                                   int lo_dtype, hipStream_t s);
 
@@ -60,7 +61,7 @@ hipError_t launch_ir_inner2_items(const BlockDesc* blocks, const Item* items, in
 hipError_t launch_sweep3(OneBlock one, int tile_y, int z_chunk, bool src, hipStream_t s, uint32_t pace = 0);
 hipError_t launch_sweep3_items(const BlockDesc* blocks, const Item* items, int nitems, int parity, int tile_y,
                                bool src, hipStream_t s);
-// The same for the refinement correction.
+// The same for the refinement correction, work lists as for two sweeps.
 hipError_t launch_ir_inner3(OneBlock one, int tile_y, int z_chunk, int lo_dtype, hipStream_t s, uint32_t pace = 0);
 hipError_t launch_ir_inner3_items(const BlockDesc* blocks, const Item* items, int nitems, int qparity, int tile_y,
                                   int lo_dtype, hipStream_t s);

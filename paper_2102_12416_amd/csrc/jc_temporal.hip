@@ -584,13 +584,13 @@ int one_block_tiles(OneBlock& one, int tile_y, int z_chunk)
     return (int)n;
 }
 
-template <typename T, int FIELD, int TY, bool SRC>
+template <typename T, int FIELD, int TXP, int TY, bool SRC>
 hipError_t sweep2_launch(const OneBlock& one, const BlockDesc* blocks, const Item* items, int parity, int n, hipStream_t s,
                          uint32_t pace)
 {
     const int grid = (n + 7) / 8 * 8;
-    hipLaunchKernelGGL((k_sweep2<T, FIELD, 32, TY, SRC>), dim3(grid), dim3((34 * (TY + 4) + 63) / 64 * 64), 0, s, one,
-                       blocks, items, parity, n, pace);
+    hipLaunchKernelGGL((k_sweep2<T, FIELD, TXP, TY, SRC>), dim3(grid), dim3(((TXP + 2) * (TY + 4) + 63) / 64 * 64), 0, s,
+                       one, blocks, items, parity, n, pace);
     return hipGetLastError();
 }
 
@@ -599,20 +599,27 @@ hipError_t sweep2_rows(const OneBlock& one, const BlockDesc* blocks, const Item*
                        hipStream_t s, uint32_t pace)
 {
     switch (tile_y) {
-    case 8: return sweep2_launch<T, FIELD, 8, SRC>(one, blocks, items, parity, n, s, pace);
-    case 16: return sweep2_launch<T, FIELD, 16, SRC>(one, blocks, items, parity, n, s, pace);
-    case 24: return sweep2_launch<T, FIELD, 24, SRC>(one, blocks, items, parity, n, s, pace);
+    case 8: return sweep2_launch<T, FIELD, 32, 8, SRC>(one, blocks, items, parity, n, s, pace);
+    case 16: return sweep2_launch<T, FIELD, 32, 16, SRC>(one, blocks, items, parity, n, s, pace);
+    case 24: return sweep2_launch<T, FIELD, 32, 24, SRC>(one, blocks, items, parity, n, s, pace);
+    case 32:
+        // a work list of 32-cell tiles
+        if constexpr (sizeof(T) < 8)
+            return items ? sweep2_launch<T, FIELD, 16, 32, SRC>(one, blocks, items, parity, n, s, pace)
+                         : hipErrorInvalidValue;
+        else
+            return hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
     }
 }
 
-template <typename T, int FIELD, int TY, bool SRC>
+template <typename T, int FIELD, int TXP, int TY, bool SRC>
 hipError_t sweep3_launch(const OneBlock& one, const BlockDesc* blocks, const Item* items, int parity, int n, hipStream_t s,
                          uint32_t pace)
 {
     const int grid = (n + 7) / 8 * 8;
-    hipLaunchKernelGGL((k_sweep3<T, FIELD, 32, TY, SRC>), dim3(grid), dim3((36 * (TY + 6) + 63) / 64 * 64), 0, s, one,
-                       blocks, items, parity, n, pace);
+    hipLaunchKernelGGL((k_sweep3<T, FIELD, TXP, TY, SRC>), dim3(grid), dim3(((TXP + 4) * (TY + 6) + 63) / 64 * 64), 0, s,
+                       one, blocks, items, parity, n, pace);
     return hipGetLastError();
 }
 
@@ -621,8 +628,15 @@ hipError_t sweep3_rows(const OneBlock& one, const BlockDesc* blocks, const Item*
                        hipStream_t s, uint32_t pace)
 {
     switch (tile_y) {
-    case 8: return sweep3_launch<T, FIELD, 8, SRC>(one, blocks, items, parity, n, s, pace);
-    case 16: return sweep3_launch<T, FIELD, 16, SRC>(one, blocks, items, parity, n, s, pace);
+    case 8: return sweep3_launch<T, FIELD, 32, 8, SRC>(one, blocks, items, parity, n, s, pace);
+    case 16: return sweep3_launch<T, FIELD, 32, 16, SRC>(one, blocks, items, parity, n, s, pace);
+    case 32:
+        // a work list of 32-cell tiles
+        if constexpr (sizeof(T) < 8)
+            return items ? sweep3_launch<T, FIELD, 16, 32, SRC>(one, blocks, items, parity, n, s, pace)
+                         : hipErrorInvalidValue;
+        else
+            return hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
     }
 }
