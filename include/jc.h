@@ -409,8 +409,10 @@ int jc_set_tiles(jc_ctx* ctx, int tile_x, int tile_y, int z_chunk);
 int jc_set_temporal_tiles(jc_ctx* ctx, int rows, int z_chunk);
 /* out = {sweeps per launch (2 or 3; 0 without temporal blocking), rows,
  * planes per work-group} of the multi-sweep launch.  Until set (jc_set_temporal_tiles or jc_autotune), the shape
- * is the library's default for the grid (16 rows; 8 for three sweeps of a
- * large bfloat16 correction); with a z_chunk given at creation or by
+ * is the library's default for the grid (16 rows); three sweeps of a large
+ * binary32 or bfloat16 correction then run in tiles of 64 cells by 32 rows
+ * with planes of their own, as they do where jc_autotune finds that faster,
+ * and this is the shape of the two-sweep launches beside them.  With a z_chunk given at creation or by
  * jc_set_tiles it is 16 rows and the planes follow z_chunk, at least 32,
  * halved (down to 8) while a launch would have fewer than 1024
  * work-groups. */

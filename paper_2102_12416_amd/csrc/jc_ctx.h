@@ -116,6 +116,7 @@ inline bool two_step_rows_ok(int rows)
     return ok;
 }
 inline bool three_step_rows_ok(int rows) { return rows == 8 || rows == 16; }
+constexpr int kQuadRows = 32;                     // of the quad tile (k_sweep3q, 64 cells wide)
 
 }  // namespace jc_rt
 
@@ -139,6 +140,9 @@ struct jc_ctx {
     // temporal blocking: rows and planes of the two-sweep work-group
     // (t2_zc 0: the one-sweep z_chunk, at least kTwoStepMinZ)
     int t2_rows = jc_rt::kTwoStepRows;
+    // three sweeps per launch by quads of cells (binary32 / bfloat16
+    // correction): planes per work-group, 0 = by pairs in the shape above
+    int quad_zc = 0;
     int t2_zc = 0;
     bool t2_auto = false;           // the shape is default_multi_shape's
     // pace of the one-sweep launches of the solve loop (jc_set_pace): ticks
@@ -230,6 +234,8 @@ namespace jc_rt {
 // The context sweeps binary32 or bfloat16 storage (the refinement's
 // correction): its tiles are at most 64 cells wide.
 inline bool narrow_storage(const jc_ctx* c) { return c->opt.ir_enable && c->opt.ir_dtype != JC_F64; }
+// Whether three sweeps of the context's correction can go by quads of cells.
+inline bool quad_sweeps(const jc_ctx* c) { return narrow_storage(c) && c->depth() == 3; }
 
 hipEvent_t take_event(jc_ctx* c);
 int drain_timing(jc_ctx* c);

@@ -40,6 +40,7 @@ struct Class {
     size_t item2_0 = 0;              // first joint multi-sweep item
     std::vector<Item> items2;        // multi-sweep tiles (groups that sweep two or three times per launch)
     int multi[3] = {64, 16, jc_rt::kTwoStepMinZ};    // their cells, rows and planes
+    bool quads = false;              // three sweeps of a binary32 correction by quads of cells
     std::vector<int> members;
     // resident sweeps: one item per member, the largest blocks first, so
     // that the last work-groups to start are the shortest
@@ -148,6 +149,12 @@ int prime_faces(jc_group* g)
 // us, binary32 31 -> 13; 56 of edge 32 28 -> 16 and 31 -> 11; 24 of edge 96 75
 // (as before) and 62 -> 49; 48 of edge 96 in bfloat16 118 -> 77.
 //
+// Binary32 classes of more work-groups than compute units sweep these tiles by
+// quads of cells (k_sweep3q; fewer waves, so two work-groups share a compute
+// unit): 24 of edge 96 48 -> 41 us, 48 of edge 64 37 -> 26, 32 of edge 128 133
+// -> 128.  In one round pairs are faster (8 of edge 96 23 against 25, 56 of edge
+// 32 10.9 against 11.4), and bfloat16 gains and loses (38 -> 28 and 78 -> 94).
+//
 // A given tile keeps 64 x 16 cells by its z chunk, at least kTwoStepMinZ; so
 // does a class of more than kMultiSearchItems such tiles, whose rounds are many
 // and hardly depend on the planes.
@@ -189,6 +196,7 @@ void multi_shape(const jc_group* g, Class& k)
                 k.multi[0] = shapes[i][0];
                 k.multi[1] = shapes[i][1];
                 k.multi[2] = planes;
+                k.quads = depth == 3 && k.ir && k.lo == JC_F32 && n > jc_rt::kComputeUnits;
             }
         }
 }
@@ -203,6 +211,7 @@ void multi_items(jc_group* g, bool search)
         k.multi[0] = 64;
         k.multi[1] = 16;
         k.multi[2] = std::max(g->tile[2], jc_rt::kTwoStepMinZ);
+        k.quads = false;
         if (search)
             multi_shape(g, k);
         k.items2.clear();
@@ -281,6 +290,9 @@ int group_sweep3(jc_group* g)
         if (!k.ir)
             e = jc::launch_sweep3_items(g->d_desc(), g->d_items2() + k.item2_0, (int)k.items2.size(), g->parity,
                                         k.multi[1], k.src, g->stream);
+        else if (k.quads)
+            e = jc::launch_ir_inner3_quad_items(g->d_desc(), g->d_items2() + k.item2_0, (int)k.items2.size(),
+                                                g->members[k.members[0]]->ir_q, k.multi[1], g->stream);
         else
             e = jc::launch_ir_inner3_items(g->d_desc(), g->d_items2() + k.item2_0, (int)k.items2.size(),
                                            g->members[k.members[0]]->ir_q, k.multi[1], k.lo, g->stream);

@@ -239,20 +239,24 @@ void build_items(jc_ctx* c)
 // against 443, and jc_autotune's own shapes at 512^3 and 512 x 768 x 1536.
 //
 // The bfloat16 correction moves few bytes per instruction and is bound by
-// issue, so from 2^23 cells on several work-groups share a compute unit: two
-// of 16 rows (two sweeps per launch, 512^3: 16 x 256 177 us per sweep, 16 x 512
-// 207) or four of 8 rows (three, 512^3: 8 x 256 186, 16 x 512 199; 1024^3: 1.99
-// ms against 2.13).
-void default_multi_shape(jc_ctx* c)
+// issue, so from 2^23 cells on two work-groups share a compute unit where two
+// sweeps go into a launch (512^3: 16 x 256 177 us per sweep, 16 x 512 207).
+//
+// Three sweeps of a binary32 or bfloat16 correction go by quads of cells
+// (k_sweep3q, 64 cells by 32 rows) from 2^22 cells on, planes by the same rule.
+// Per sweep with the outer step, quads against the best pairs: 512^3 binary32
+// 190 us against 221, bfloat16 175 against 187; 385 x 250 x 333 57 against 67,
+// 54 against 55; 200 x 180 x 160 11.2 against 12.5, 11.6 against 12.8; below,
+// fewer and longer-stepping work-groups lose (128^3 5.9 against 5.8, 64^3 3.7
+// against 3.5).
+constexpr int64_t kQuadCells = (int64_t)1 << 22;
+
+// The planes that take the fewest rounds x steps.
+int multi_planes(int64_t depth_z, int64_t tiles, int64_t slots, int sweeps)
 {
-    const HostBlock& b = c->blocks[0];
-    const bool issue_bound = c->opt.ir_enable && c->opt.ir_dtype == JC_BF16 &&
-                             b.n[0] * b.n[1] * b.n[2] >= ((int64_t)1 << 23);
-    const int64_t slots = (int64_t)kComputeUnits * (!issue_bound ? 1 : c->depth() == 3 ? 4 : 2);
-    c->t2_rows = issue_bound && c->depth() == 3 ? 8 : kTwoStepRows;
-    const int64_t nz = std::min<int64_t>(b.n[2], 1 << 20);
-    const int64_t tiles = (b.n[0] + 63) / 64 * ((b.n[1] + c->t2_rows - 1) / c->t2_rows);
+    const int64_t nz = std::min<int64_t>(depth_z, 1 << 20);
     double best = 0;
+    int planes = 1;
     for (int64_t k = 1; k <= nz; ++k) {
         const int64_t zc = (nz + k - 1) / k;
         const int64_t n = tiles * ((nz + zc - 1) / zc);
@@ -260,12 +264,25 @@ void default_multi_shape(jc_ctx* c)
         if (k > 1 && zc < kMinZChunk && n > slots)
             break;
         const int64_t rounds = (n + slots - 1) / slots;
-        const double cost = (double)rounds * (double)(zc + 2 * c->depth()) * (rounds > 1 ? 1.15 : 1.0);
+        const double cost = (double)rounds * (double)(zc + 2 * sweeps) * (rounds > 1 ? 1.15 : 1.0);
         if (best == 0 || cost < best) {
             best = cost;
-            c->t2_zc = (int)zc;
+            planes = (int)zc;
         }
     }
+    return planes;
+}
+
+void default_multi_shape(jc_ctx* c)
+{
+    const HostBlock& b = c->blocks[0];
+    const int64_t cells = b.n[0] * b.n[1] * b.n[2], tx = (b.n[0] + 63) / 64;
+    const bool issue_bound = c->opt.ir_enable && c->opt.ir_dtype == JC_BF16 && cells >= ((int64_t)1 << 23);
+    c->t2_rows = kTwoStepRows;
+    c->t2_zc = multi_planes(b.n[2], tx * ((b.n[1] + c->t2_rows - 1) / c->t2_rows),
+                            (int64_t)kComputeUnits * (issue_bound ? 2 : 1), c->depth());
+    if (quad_sweeps(c) && cells >= kQuadCells)
+        c->quad_zc = multi_planes(b.n[2], tx * ((b.n[1] + kQuadRows - 1) / kQuadRows), kComputeUnits, 3);
     c->t2_auto = true;
 }
 
@@ -716,6 +733,10 @@ int two_step_chunk(const jc_ctx* c)
     return (int)zc;
 }
 
+// Rows and planes of the launch that the solve loop of a temporal context runs.
+int multi_rows(const jc_ctx* c) { return c->quad_zc > 0 ? jc_rt::kQuadRows : c->t2_rows; }
+int multi_chunk(const jc_ctx* c) { return c->quad_zc > 0 ? c->quad_zc : two_step_chunk(c); }
+
 // The pace of a temporal context belongs to its deepest launch (the one its
 // solve loop runs); the other launches run unpaced.
 uint32_t multi_pace(const jc_ctx* c, int depth) { return c->depth() == depth ? c->pace : 0u; }
@@ -758,13 +779,16 @@ hipError_t launch_three_step(jc_ctx* c, int rows, int zc, uint32_t pace)
 }
 hipError_t launch_three_step(jc_ctx* c, int rows, int zc) { return launch_three_step(c, rows, zc, multi_pace(c, 3)); }
 
+// rows kQuadRows: by quads of cells.
 hipError_t launch_ir_three_step(jc_ctx* c, int qparity, int rows, int zc, uint32_t pace)
 {
+    if (rows == jc_rt::kQuadRows)
+        return jc::launch_ir_inner3_quads(one_block_lo(c, qparity), zc, c->opt.ir_dtype, c->stream, pace);
     return jc::launch_ir_inner3(one_block_lo(c, qparity), rows, zc, c->opt.ir_dtype, c->stream, pace);
 }
-hipError_t launch_ir_three_step(jc_ctx* c, int qparity, int rows, int zc)
+hipError_t launch_ir_three_step(jc_ctx* c, int qparity)
 {
-    return launch_ir_three_step(c, qparity, rows, zc, multi_pace(c, 3));
+    return launch_ir_three_step(c, qparity, multi_rows(c), multi_chunk(c), multi_pace(c, 3));
 }
 
 // Launches that run n sweeps at depth d (sweeps per launch): n / d full
@@ -1097,6 +1121,8 @@ int tune_two_step(jc_ctx* c, int reps)
         row_cands.assign(std::begin(jc_rt::kThreeStepRowCandidates), std::end(jc_rt::kThreeStepRowCandidates));
     else
         row_cands.assign(std::begin(jc_rt::kTwoStepRowCandidates), std::end(jc_rt::kTwoStepRowCandidates));
+    if (jc_rt::quad_sweeps(c))
+        row_cands.push_back(jc_rt::kQuadRows);
     for (int rows : row_cands)
         for (int nch : {1, 2, 3, 4, 6, 8, 12, 16}) {
             const int zc = (int)((nz + nch - 1) / nch);
@@ -1158,8 +1184,14 @@ int tune_two_step(jc_ctx* c, int reps)
     if (st != JC_OK)
         return st;
     const Cand best = *std::min_element(cand.begin(), cand.end(), [](const Cand& a, const Cand& b) { return a.ms < b.ms; });
-    c->t2_rows = best.rows;
-    c->t2_zc = best.zc;
+    if (best.rows == jc_rt::kQuadRows) {
+        c->quad_zc = best.zc;              // the two-sweep launches keep their shape
+        c->t2_zc = two_step_chunk(c);
+    } else {
+        c->quad_zc = 0;
+        c->t2_rows = best.rows;
+        c->t2_zc = best.zc;
+    }
     c->t2_auto = false;
     c->pace = 0;
     free_graphs(c);
@@ -1683,7 +1715,7 @@ int jc_solve_ir(jc_ctx* c, int inner_sweeps, double rtol, int64_t max_inner, jc_
             if (c->depth() == 3) {
                 for (; j + 3 <= m && s2 == JC_OK; j += 3) {
                     s2 = timed(c, JC_K_IR_INNER,
-                               [&] { return launch_ir_three_step(c, qq, c->t2_rows, two_step_chunk(c)); });
+                               [&] { return launch_ir_three_step(c, qq); });
                     qq ^= 1;
                 }
             }
@@ -1771,6 +1803,7 @@ int jc_set_tiles(jc_ctx* c, int tile_x, int tile_y, int z_chunk)
         c->t2_auto = false;
         c->t2_rows = kTwoStepRows;
         c->t2_zc = 0;
+        c->quad_zc = 0;
     }
     build_items(c);
     c->hranges[1] = (int32_t)c->items.size();
@@ -1797,6 +1830,7 @@ int jc_set_temporal_tiles(jc_ctx* c, int rows, int z_chunk)
         return fail(JC_ERR_INVALID, "z_chunk must be >= 1");
     c->t2_rows = rows;
     c->t2_zc = z_chunk;
+    c->quad_zc = 0;
     c->t2_auto = false;
     c->pace = 0;                           // a pace belongs to a shape
     free_graphs(c);                        // graphs hold the old launch shapes
@@ -1854,9 +1888,9 @@ int tune_pace(jc_ctx* c, int reps, double warm_ms, int64_t out[3])
     if (depth > 1) {
         // the multi-sweep launch of a one-block temporal context
         const HostBlock& b = c->blocks[0];
-        const int zc = two_step_chunk(c);
+        const int rows = multi_rows(c), zc = multi_chunk(c);
         zmax = zc;
-        nit = ((b.n[0] + 63) / 64) * ((b.n[1] + c->t2_rows - 1) / c->t2_rows) * ((b.n[2] + zc - 1) / zc);
+        nit = ((b.n[0] + 63) / 64) * ((b.n[1] + rows - 1) / rows) * ((b.n[2] + zc - 1) / zc);
     }
     const int64_t rounds = ncu > 0 ? (nit + ncu - 1) / ncu : 1;
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1873,7 +1907,8 @@ int tune_pace(jc_ctx* c, int reps, double warm_ms, int64_t out[3])
         auto one = [&]() -> hipError_t {
             const int zc = two_step_chunk(c);
             if (depth == 3)
-                return ir ? launch_ir_three_step(c, 1, c->t2_rows, zc, pace) : launch_three_step(c, c->t2_rows, zc, pace);
+                return ir ? launch_ir_three_step(c, 1, multi_rows(c), multi_chunk(c), pace)
+                          : launch_three_step(c, c->t2_rows, zc, pace);
             if (depth == 2)
                 return ir ? launch_ir_two_step(c, 1, c->t2_rows, zc, pace) : launch_two_step(c, c->t2_rows, zc, pace);
             return ir ? jc::launch_ir_inner(c->d_blocks(), c->d_items(), (int)nit, 1, c->tile_x, c->tile_y,

@@ -66,6 +66,14 @@ hipError_t launch_ir_inner3(OneBlock one, int tile_y, int z_chunk, int lo_dtype,
 hipError_t launch_ir_inner3_items(const BlockDesc* blocks, const Item* items, int nitems, int qparity, int tile_y,
                                   int lo_dtype, hipStream_t s);
 
+// Three sweeps of the binary32 or bfloat16 correction by quads of cells
+// (k_sweep3q), tiles of 64 cells by 32 rows.
+hipError_t launch_ir_inner3_quads(OneBlock one, int z_chunk, int lo_dtype, hipStream_t s, uint32_t pace = 0);
+// The same in binary32 over a work list of 64 x 16 (tile_y 16) or 32 x 32 cells
+// (tile_y 32).
+hipError_t launch_ir_inner3_quad_items(const BlockDesc* blocks, const Item* items, int nitems, int qparity, int tile_y,
+                                       hipStream_t s);
+
 // Many sweeps in one launch (k_resident): nsweeps Jacobi sweeps of blocks
 // that fit on chip (resident_fits), one work-group per block, iterate k from
 // copy parity (xor the item's flip), iterate k + nsweeps into copy parity ^

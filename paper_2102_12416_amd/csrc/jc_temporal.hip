@@ -567,6 +567,279 @@ k_sweep3(OneBlock one, const BlockDesc* __restrict__ blocks, const Item* __restr
 }
 // ---- three-step sweep: end ----
 
+// ---- three sweeps of a correction in quads: begin ----
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+// Four cells (an aligned quad: cell x = 1 of a row starts a line) as stored.
+template <typename T> struct Quad;
+
+template <> struct Quad<float> {
+    __device__ static v4f ld(const float* p) { return *(const v4f JC_GLOBAL*)(p); }
+    __device__ static void stn(float* p, v4f v) { __builtin_nontemporal_store(v, (v4f JC_GLOBAL*)(p)); }
+    __device__ static v4f round(v4f v) { return v; }
+};
+
+template <> struct Quad<bf16> {
+    typedef uint32_t W __attribute__((ext_vector_type(2)));
+    __device__ static v4f unpack(W w) { return v4f{bf16_lo(w.x), bf16_hi(w.x), bf16_lo(w.y), bf16_hi(w.y)}; }
+    __device__ static W pack(v4f v) { return W{bf16_pair(v.x, v.y), bf16_pair(v.z, v.w)}; }
+    __device__ static v4f ld(const bf16* p) { return unpack(*(const W JC_GLOBAL*)(p)); }
+    __device__ static void stn(bf16* p, v4f v) { __builtin_nontemporal_store(pack(v), (W JC_GLOBAL*)(p)); }
+    __device__ static v4f round(v4f v) { return unpack(pack(v)); }
+};
+
+// k_sweep3 for the binary32 and bfloat16 correction (with its source r_lo), a
+// tile of 4 TXQ cells by TY rows: four cells per thread instead of two.
+// k_sweep3 in these formats is bound by instruction issue, a third of it LDS
+// accesses; a quad needs one write, two whole neighbours and two single cells
+// per level where two pairs need two writes and eight neighbours, shares its
+// addresses and masks, and one quad left and right covers the three-cell ring.
+// A tile of 32 rows then fits 11 waves and reads 1.33 quads per quad of the
+// tile (16 rows: 1.53).  Cells outside the block do not take part in the test
+// for the IEEE division: their sums are often zero (zero ghosts, zero padding
+// behind a ragged row), which cost every step of such a tile the division.
+// Waves whose cells are all inside skip the selection of ghosts.
+//
+// Per sweep with the outer step, against k_sweep3 in its best shape: 512^3
+// binary32 221 -> 190 us, bfloat16 187 -> 175; 385 x 250 x 333 67 -> 57 and 55
+// -> 54 (with the test over all cells 64 and 61); 1024^3 binary32 1.89 -> 1.56
+// ms.  The launch alone moves 12 bytes a cell in binary32 at 4.7 TB/s, the
+// card's copy rate; in bfloat16 it is still bound by issue.  Tiles of 8, 16
+// and 24 rows: 222, 203 and 223 us in binary32 at 512^3.
+constexpr int quad_threads(int txq, int ty) { return (txq * ty + 6 * txq + 2 * ty + 8 + 63) / 64 * 64; }
+
+template <typename T, int TXQ, int TY>
+__global__ void __launch_bounds__(quad_threads(TXQ, TY))
+k_sweep3q(OneBlock one, const BlockDesc* __restrict__ blocks, const Item* __restrict__ items, int parity, int ntiles,
+          uint32_t pace)
+{
+    using F = Fld<T, FIELD_D>;
+    constexpr int EP = TXQ + 2;                   // quads of an extended row
+    constexpr int ER = TY + 6;                    // extended rows
+    constexpr int NTILE = TXQ * TY;               // tile threads
+    constexpr int NMID = NTILE + 2 * TXQ + 2 * TY;
+    constexpr int NL1 = NMID + 2 * TXQ + 4;
+    static_assert(NTILE % 64 == 0, "tile threads are whole waves");
+    constexpr int LN = ER * EP;                   // quads of an LDS plane; quad LN: sink of idle lanes
+    __shared__ v4f A[2][LN + 1];                  // iterate k
+    __shared__ v4f Bn[2][LN + 1];                 // iterate k + 1
+    __shared__ v4f Cn[2][LN + 1];                 // iterate k + 2
+
+    const int id = logical_block(blockIdx.x, gridDim.x);
+    if (id >= ntiles)
+        return;                                   // uniform over the work-group
+    const uint64_t pace_t0 = pace ? __builtin_amdgcn_s_memrealtime() : 0;
+    const T *src, *source;
+    T* out;
+    int64_t pitch, plane;
+    int nx, ny, nz, x0, y0, zf, zl;
+    if (items) {
+        const Item it = items[id];
+        const BlockDesc* B = blocks + it.block;
+        const int p = parity ^ it.flip;
+        src = F::src(B, p);
+        out = F::dst(B, p);
+        source = F::source(B);
+        pitch = F::pitch(B);
+        plane = F::plane(B);
+        nx = B->n[0];
+        ny = B->n[1];
+        nz = B->n[2];
+        x0 = it.x0;
+        y0 = it.y0;
+        zf = it.z0 + 1;
+        zl = it.z0 + it.zlen;
+    } else {
+        src = static_cast<const T*>(one.src);
+        out = static_cast<T*>(one.dst);
+        source = static_cast<const T*>(one.source);
+        pitch = one.pitch;
+        plane = one.plane;
+        nx = one.nx;
+        ny = one.ny;
+        nz = one.nz;
+        const uint32_t row = (uint32_t)id / (uint32_t)one.tiles_x;
+        const int chunk = (int)(row / (uint32_t)one.tiles_y);
+        x0 = (int)((uint32_t)id - row * (uint32_t)one.tiles_x) * (4 * TXQ);
+        y0 = ((int)row - chunk * one.tiles_y) * TY;
+        zf = chunk * one.planes + min(chunk, one.rest) + 1;
+        zl = zf + one.planes - (chunk < one.rest ? 0 : 1);
+    }
+
+    // this thread's quad (j, r) of the extended region
+    const int t = threadIdx.x;
+    int j = 1, r = 3;
+    bool live = true;
+    if (t < NTILE) {
+        j = 1 + t % TXQ;
+        r = 3 + t / TXQ;
+    } else {
+        int q = t - NTILE;
+        if (q < 2 * TXQ) {                        // the rows next to the tile
+            j = 1 + q % TXQ;
+            r = q < TXQ ? 2 : TY + 3;
+        } else if ((q -= 2 * TXQ) < 2 * TY) {     // the quads left and right of its rows
+            j = (q & 1) ? EP - 1 : 0;
+            r = 3 + (q >> 1);
+        } else if ((q -= 2 * TY) < 2 * TXQ) {     // second ring: rows 1 and ER - 2
+            j = 1 + q % TXQ;
+            r = q < TXQ ? 1 : ER - 2;
+        } else if ((q -= 2 * TXQ) < 4) {          // and the corners of the first
+            j = (q & 1) ? EP - 1 : 0;
+            r = (q & 2) ? TY + 3 : 2;
+        } else if ((q -= 4) < 2 * TXQ) {          // third ring: rows 0 and ER - 1
+            j = 1 + q % TXQ;
+            r = q < TXQ ? 0 : ER - 1;
+        } else if ((q -= 2 * TXQ) < 4) {          // and the corners of the second
+            j = (q & 1) ? EP - 1 : 0;
+            r = (q & 2) ? ER - 2 : 1;
+        } else {
+            live = false;
+        }
+    }
+    const bool tile = t < NTILE;                  // uniform over each wave
+    const bool mid = t < NMID;
+    const bool l1 = (t & ~63) < NL1;              // the waves that hold a thread of the first stage
+    const int xs = x0 - 3 + 4 * j;                // cells xs .. xs + 3 (xs = 1 mod 4, >= -3)
+    const int ye = y0 - 2 + r;
+    const int xs_c = min(xs, (nx & ~3) + 1);      // last quad holding a cell <= nx + 1
+    const int ye_c = min(max(ye, 0), ny + 1);
+    const bool y_in = live && ye >= 1 && ye <= ny;
+    const bool in0 = y_in && xs >= 1 && xs <= nx;
+    const bool in1 = y_in && xs + 1 >= 1 && xs + 1 <= nx;
+    const bool in2 = y_in && xs + 2 >= 1 && xs + 2 <= nx;
+    const bool in3 = y_in && xs + 3 >= 1 && xs + 3 <= nx;
+    // a tile quad is stored whole where it ends at nx + 1 or before, else its
+    // first pair: what lies behind a row's x = nx + 1 ghost is not its own
+    const bool st4 = tile && ye <= ny && xs + 2 <= nx;
+    const bool st2 = tile && ye <= ny && xs <= nx && !st4;
+    const int64_t rowoff = (int64_t)ye_c * pitch + xs_c;
+    const T* __restrict__ col = src + rowoff;
+    const T* __restrict__ scol = source + rowoff;
+    T* __restrict__ dst = out + rowoff;
+
+    // LDS quads: own, left, right, above, below; at the rim of the region
+    // (results not used) its own instead of one outside
+    const int pn = r * EP + j;
+    const int pw = live ? pn : LN;                // the quad this thread writes
+    const int pl = j > 0 ? pn - 1 : pn, pr = j < EP - 1 ? pn + 1 : pn;
+    const int pu = r > 0 ? pn - EP : pn, pd = r < ER - 1 ? pn + EP : pn;
+
+    // register rings as in k_sweep3
+    constexpr int PD = 3;
+    constexpr int RS = 6;
+    const int zlo = max(zf - 3, 0);               // first plane read
+    const int zhi = min(zl + 3, nz + 1);          // last plane read
+    v4f u[RS], b[RS], v[3], w[3];
+#pragma unroll
+    for (int k = 0; k < RS; ++k)
+        b[k] = v4f(0.0f);
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        v[k] = w[k] = v4f(0.0f);
+    u[RS - 1] = Quad<T>::ld(col + (int64_t)zlo * plane);
+    b[RS - 1] = Quad<T>::ld(scol + (int64_t)zlo * plane);
+#pragma unroll
+    for (int k = 0; k < PD; ++k) {
+        const int64_t zk = (int64_t)min(max(zf - 2 + k, 0), zhi) * plane;
+        u[k] = Quad<T>::ld(col + zk);
+        b[k] = Quad<T>::ld(scol + zk);
+    }
+
+    // the update of `c` from its plane P of the level below, its z neighbours
+    // and source
+    auto update = [&](const v4f* P, v4f c, v4f zm, v4f zp, v4f s) {
+        const v4f ym = P[pu], yp = P[pd];
+        const float* const Pf = reinterpret_cast<const float*>(P);
+        const float xm = Pf[4 * pl + 3], xp = Pf[4 * pr];
+        v4f a{xm + c.y, c.x + c.z, c.y + c.w, c.z + xp};
+        a = a + ym;
+        a = a + yp;
+        a = a + zm;
+        a = a + zp;
+        a = a + s;
+        v4f n{div6_fast(a.x), div6_fast(a.y), div6_fast(a.z), div6_fast(a.w)};
+        const bool r0 = in0 && div6_redo(n.x), r1 = in1 && div6_redo(n.y);
+        const bool r2 = in2 && div6_redo(n.z), r3 = in3 && div6_redo(n.w);
+        if (__builtin_expect(r0 || r1 || r2 || r3, 0)) {
+            n.x = r0 ? a.x / 6.0f : n.x;
+            n.y = r1 ? a.y / 6.0f : n.y;
+            n.z = r2 ? a.z / 6.0f : n.z;
+            n.w = r3 ? a.w / 6.0f : n.w;
+        }
+        return Quad<T>::round(n);
+    };
+    const bool inner = __all(in0 && in1 && in2 && in3);
+    auto keep = [&](v4f n, v4f o, bool z_in) {
+        if (inner && z_in)                        // uniform over the wave
+            return n;
+        return v4f{in0 && z_in ? n.x : o.x, in1 && z_in ? n.y : o.y, in2 && z_in ? n.z : o.z, in3 && z_in ? n.w : o.w};
+    };
+    // STAGES: 1 = iterate k + 1 only, 2 = also k + 2, 3 = also k + 3
+    const int s_first = zf - 2;
+    auto step = [&](int s, auto kc, auto stages) {
+        constexpr int K = decltype(kc)::value;
+        constexpr int ST = decltype(stages)::value;
+        constexpr int SM = (K + RS - 1) % RS, SC = K, SP = (K + 1) % RS, SQ = (K + PD) % RS;
+        constexpr int S2 = (K + RS - 2) % RS;     // plane s - 2
+        constexpr int VC = K % 3, VM = (K + 2) % 3, VMM = (K + 1) % 3;
+        constexpr int HC = K & 1;
+        if (pace)
+            pace_wait(pace_t0 + (uint64_t)(s - s_first) * pace);
+        const int64_t zq = (int64_t)min(s + PD, zhi) * plane;
+        u[SQ] = Quad<T>::ld(col + zq);
+        b[SQ] = Quad<T>::ld(scol + zq);
+        A[HC][pw] = u[SC];
+        __syncthreads();
+        // iterate k + 1 at plane s
+        if (l1) {
+            v[VC] = keep(update(A[HC], u[SC], u[SM], u[SP], b[SC]), u[SC], s >= 1 && s <= nz);
+            Bn[HC][pw] = v[VC];
+        }
+        // iterate k + 2 at plane s - 1
+        if (ST >= 2 && mid) {
+            w[VC] = keep(update(Bn[HC ^ 1], v[VM], v[VMM], v[VC], b[SM]), v[VM], s - 1 >= 1 && s - 1 <= nz);
+            Cn[HC][pw] = w[VC];
+        }
+        // iterate k + 3 at plane s - 2
+        if (ST >= 3 && tile) {
+            const v4f n = update(Cn[HC ^ 1], w[VM], w[VMM], w[VC], b[S2]);
+            // the x = nx + 1 ghost behind a row's last cell keeps its value
+            const v4f o = keep(n, u[S2], true);
+            if (st4)
+                Quad<T>::stn(dst + (int64_t)(s - 2) * plane, o);
+            else if (st2)
+                Tr<T>::stn(dst + (int64_t)(s - 2) * plane, o.x, o.y);
+        }
+    };
+    using One = std::integral_constant<int, 1>;
+    using Two = std::integral_constant<int, 2>;
+    using Three = std::integral_constant<int, 3>;
+    int s = zf - 2;
+    step(s, std::integral_constant<int, 0>{}, One{});
+    step(s + 1, std::integral_constant<int, 1>{}, One{});
+    step(s + 2, std::integral_constant<int, 2>{}, Two{});
+    step(s + 3, std::integral_constant<int, 3>{}, Two{});
+    s += 4;
+#define JC_STEP3(k) step(s + (k), std::integral_constant<int, ((k) + 4) % RS>{}, Three{})
+    const int s_end = zl + 2;
+    for (; s + 5 <= s_end; s += 6) {
+        JC_STEP3(0);
+        JC_STEP3(1);
+        JC_STEP3(2);
+        JC_STEP3(3);
+        JC_STEP3(4);
+        JC_STEP3(5);
+    }
+    if (s <= s_end) JC_STEP3(0);
+    if (s + 1 <= s_end) JC_STEP3(1);
+    if (s + 2 <= s_end) JC_STEP3(2);
+    if (s + 3 <= s_end) JC_STEP3(3);
+    if (s + 4 <= s_end) JC_STEP3(4);
+#undef JC_STEP3
+}
+// ---- three sweeps of a correction in quads: end ----
+
 // Fills in the tiles of a launch over one block; the work-groups, or 0 where
 // there are too many.
 int one_block_tiles(OneBlock& one, int tile_y, int z_chunk)
@@ -641,6 +914,16 @@ hipError_t sweep3_rows(const OneBlock& one, const BlockDesc* blocks, const Item*
     }
 }
 
+template <typename T, int TXQ, int TY>
+hipError_t quads_launch(const OneBlock& one, const BlockDesc* blocks, const Item* items, int parity, int n, hipStream_t s,
+                        uint32_t pace)
+{
+    const int grid = (n + 7) / 8 * 8;
+    hipLaunchKernelGGL((k_sweep3q<T, TXQ, TY>), dim3(grid), dim3(quad_threads(TXQ, TY)), 0, s, one, blocks, items, parity,
+                       n, pace);
+    return hipGetLastError();
+}
+
 // The sweeps of the iterate (with or without a source) and of the correction
 // by storage format, `ROWS` = sweep2_rows or sweep3_rows.
 #define JC_FIELD_U(ROWS, one, blocks, items, parity, n, pace)                                                   \
@@ -676,6 +959,26 @@ hipError_t launch_ir_inner3(OneBlock one, int tile_y, int z_chunk, int lo_dtype,
 {
     const int n = one_block_tiles(one, tile_y, z_chunk);
     return n < 1 ? hipErrorInvalidValue : JC_FIELD_D(sweep3_rows, one, nullptr, nullptr, 0, n, pace);
+}
+
+hipError_t launch_ir_inner3_quads(OneBlock one, int z_chunk, int lo_dtype, hipStream_t s, uint32_t pace)
+{
+    const int n = one_block_tiles(one, 32, z_chunk);
+    if (n < 1)
+        return hipErrorInvalidValue;
+    return lo_dtype == 1   ? quads_launch<float, 16, 32>(one, nullptr, nullptr, 0, n, s, pace)
+           : lo_dtype == 2 ? quads_launch<bf16, 16, 32>(one, nullptr, nullptr, 0, n, s, pace)
+                           : hipErrorInvalidValue;
+}
+
+hipError_t launch_ir_inner3_quad_items(const BlockDesc* blocks, const Item* items, int nitems, int qparity, int tile_y,
+                                       hipStream_t s)
+{
+    if (nitems <= 0)
+        return hipSuccess;
+    return tile_y == 16   ? quads_launch<float, 16, 16>(OneBlock{}, blocks, items, qparity, nitems, s, 0)
+           : tile_y == 32 ? quads_launch<float, 8, 32>(OneBlock{}, blocks, items, qparity, nitems, s, 0)
+                          : hipErrorInvalidValue;
 }
 
 hipError_t launch_sweep2_items(const BlockDesc* blocks, const Item* items, int nitems, int parity, int tile_y, bool src,

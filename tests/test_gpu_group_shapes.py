@@ -16,6 +16,7 @@ from paper_2102_12416_amd import Group, Solver  # noqa: E402
 SIZES = {
     "one": [(5, 3, 2)],
     "edges": [(31, 33, 9), (32, 32, 32), (33, 31, 65), (63, 17, 16), (64, 16, 17), (65, 15, 1), (1, 1, 7)],
+    "rounds64": [(64, 63, 48)] * 40,
     "rounds": [(97, 66, 70), (65, 33, 64)] * 13,
 }
 
