@@ -431,7 +431,8 @@ int jc_temporal_info(const jc_ctx* ctx, int64_t out[3]);
  * step rebuilds them; JC_ERR_STATE while a group's refinement step is in
  * progress on the context).  With temporal = 1 the two-sweep launch (of
  * the correction, on a context with refinement buffers) is then timed over
- * rows {8, 16, 24} x z chunks of 1/1 .. 1/16 of the depth (max(reps, 2)
+ * rows {8, 16, 24} x z chunks of 1/1 .. 1/16 of the depth, and the shape it has (kept
+ * unless another is 2 % faster; max(reps, 2)
  * launches each, the three fastest again over three rounds) and the
  * fastest kept (jc_temporal_info); the one shape serves both two-sweep
  * launches of the context.  The pace of the one-sweep launch is tuned for
