@@ -408,12 +408,13 @@ int jc_set_tiles(jc_ctx* ctx, int tile_x, int tile_y, int z_chunk);
  * was created with temporal = 1. */
 int jc_set_temporal_tiles(jc_ctx* ctx, int rows, int z_chunk);
 /* out = {sweeps per launch (2 or 3; 0 without temporal blocking), rows,
- * planes per work-group} of the multi-sweep launch.  Until set (jc_set_temporal_tiles or jc_autotune), the shape
- * is the library's default for the grid (16 rows); three sweeps of a large
- * binary32 or bfloat16 correction then run in tiles of 64 cells by 32 rows
- * with planes of their own, as they do where jc_autotune finds that faster,
- * and this is the shape of the two-sweep launches beside them.  With a z_chunk given at creation or by
- * jc_set_tiles it is 16 rows and the planes follow z_chunk, at least 32,
+ * planes per work-group} of the multi-sweep launch.  Until set
+ * (jc_set_temporal_tiles or jc_autotune), the shape is the library's default
+ * for the grid (16 rows); three sweeps of a large binary32 or bfloat16
+ * correction then run in tiles of 64 cells by 32 rows with planes of their
+ * own, as they do where jc_autotune finds that faster, and this is the shape
+ * of the two-sweep launches beside them.  With a z_chunk given at creation or
+ * by jc_set_tiles it is 16 rows and the planes follow z_chunk, at least 32,
  * halved (down to 8) while a launch would have fewer than 1024
  * work-groups. */
 int jc_temporal_info(const jc_ctx* ctx, int64_t out[3]);
@@ -431,10 +432,9 @@ int jc_temporal_info(const jc_ctx* ctx, int64_t out[3]);
  * step rebuilds them; JC_ERR_STATE while a group's refinement step is in
  * progress on the context).  With temporal = 1 the two-sweep launch (of
  * the correction, on a context with refinement buffers) is then timed over
- * rows {8, 16, 24} x z chunks of 1/1 .. 1/16 of the depth, and the shape it has (kept
- * unless another is 2 % faster; max(reps, 2)
- * launches each, the three fastest again over three rounds) and the
- * fastest kept (jc_temporal_info); the one shape serves both two-sweep
+ * rows {8, 16, 24} x z chunks of 1/1 .. 1/16 of the depth and the shape it
+ * has, which stays unless another is 2 % faster (max(reps, 2) launches
+ * each, the three fastest again over three rounds), and the fastest kept (jc_temporal_info); the one shape serves both two-sweep
  * launches of the context.  The pace of the one-sweep launch is tuned for
  * the chosen shape (jc_autotune_pace); out[3] is then the time with it.  The trial sweeps write only
  * the other ping-pong copy and face slot, so the current iterate and

@@ -140,10 +140,10 @@ struct jc_ctx {
     // temporal blocking: rows and planes of the two-sweep work-group
     // (t2_zc 0: the one-sweep z_chunk, at least kTwoStepMinZ)
     int t2_rows = jc_rt::kTwoStepRows;
+    int t2_zc = 0;
     // three sweeps per launch by quads of cells (binary32 / bfloat16
     // correction): planes per work-group, 0 = by pairs in the shape above
     int quad_zc = 0;
-    int t2_zc = 0;
     bool t2_auto = false;           // the shape is default_multi_shape's
     // pace of the one-sweep launches of the solve loop (jc_set_pace): ticks
     // of the 100 MHz constant clock per plane step; 0 = none

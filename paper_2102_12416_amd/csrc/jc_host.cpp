@@ -1885,7 +1885,7 @@ int64_t jc_get_pace(const jc_ctx* c) { return c ? (int64_t)c->pace : 0; }
 namespace {
 
 // Tune the pace of the context's solve-loop sweep for its current tile
-// shape (see pace_wait in jc_kernels.hip).  A pace only helps a launch
+// shape (see pace_wait in jc_sweep.h).  A pace only helps a launch
 // whose work-groups all run at once, or in two rounds: it holds the fast
 // ones to a common rate so that none is left running alone at the end.
 // The candidates are fractions of the plane-step time of the unpaced

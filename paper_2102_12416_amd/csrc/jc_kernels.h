@@ -17,7 +17,7 @@ constexpr int kTileX = 64;
 // slot.  resid: write one partial sum of r^2 per item into partials.
 // store: write the new iterate (false = residual only).
 // pace: ticks of the constant 100 MHz clock per plane step below which a
-// work-group waits (0 = none; see pace_wait in jc_kernels.hip).
+// work-group waits (0 = none; see pace_wait in jc_sweep.h).
 hipError_t launch_sweep(const BlockDesc* blocks, const Item* items, int nitems, int parity,
                         int tile_x, int tile_y, bool fused, bool resid, bool store, bool src, double* partials,
                         hipStream_t s, uint32_t pace = 0);
