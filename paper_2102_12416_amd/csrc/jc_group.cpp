@@ -151,9 +151,10 @@ int prime_faces(jc_group* g)
 //
 // Binary32 classes of more work-groups than compute units sweep these tiles by
 // quads of cells (k_sweep3q; fewer waves, so two work-groups share a compute
-// unit): 24 of edge 96 48 -> 41 us, 48 of edge 64 37 -> 26, 32 of edge 128 133
-// -> 128.  In one round pairs are faster (8 of edge 96 23 against 25, 56 of edge
-// 32 10.9 against 11.4), and bfloat16 gains and loses (38 -> 28 and 78 -> 94).
+// unit): 24 of edge 96 48 -> 41 us, 48 of edge 64 32 -> 26, 12 of edge 128 53 ->
+// 45, 48 of edge 96 93 -> 91.  In one round pairs are faster (8 of edge 96 20.7
+// against 24.5, 56 of edge 32 9.8 against 11.4), and bfloat16 gains and loses (48
+// of edge 64 38 -> 28, of edge 96 73 -> 94).
 //
 // A given tile keeps 64 x 16 cells by its z chunk, at least kTwoStepMinZ; so
 // does a class of more than kMultiSearchItems such tiles, whose rounds are many
