@@ -9,8 +9,9 @@ namespace jc {
 
 // Blocks that one work-group can sweep many times on chip (the resident
 // sweep kernel): at most 32 planes, (nx + 1) / 2 * ny <= 512 cell pairs
-// (one thread each), and LDS for four plane buffers plus the ghost ring
-// of every plane within 64 KiB.
+// (one thread each), and four planes plus the ghost ring of every plane
+// within 64 KiB.  This is the interface's limit; the kernel's own buffers
+// (below) round both up and hold every shape within it.
 constexpr int kResidentMaxPlanes = 32;
 constexpr int kResidentMaxPairs = 512;
 constexpr int64_t kResidentMaxLds = 65536;
@@ -36,9 +37,13 @@ inline constexpr int64_t resident_region_bytes(int64_t nx, int64_t ny, int64_t n
     return 16 * ((ep * ny + 63) / 64 * 64 + (nz + 3) / 4 * (2 * ep + ny));
 }
 
-// Buffer sizes the kernel is built for: up to 16^3 (eight work-groups on a
-// compute unit), up to 32^3, and every shape that fits.
-constexpr int kResidentRegions[3] = {4096, 16384, 24832};
+// Buffer sizes the kernel is built for.  Its registers let 8 waves share a
+// compute unit, so these are the largest buffers of which 8, 6, 4 and 2
+// work-groups of fewer waves share its 160 KiB, and every shape that fits.  (With
+// 16 KiB for every shape above 16^3 two work-groups of 16 x 10 x 32 cells, of two
+// waves each, shared a compute unit: 9.7 us per sweep of 1024 of them, 6.3 now,
+// with a source 10.9 and 7.1.)
+constexpr int kResidentRegions[5] = {5120, 6656, 10240, 20480, 24832};
 
 // What a launch has to hold: the largest of each over the blocks it sweeps.
 struct ResidentShape {

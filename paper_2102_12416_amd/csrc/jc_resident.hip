@@ -443,9 +443,11 @@ hipError_t launch_resident(const BlockDesc* blocks, const Item* items, int nitem
         return hipGetLastError();                                                                               \
     }
     JC_RESIDENT_CASE(0, false)
-    JC_RESIDENT_CASE(1, true)
     JC_RESIDENT_CASE(1, false)
     JC_RESIDENT_CASE(2, false)
+    JC_RESIDENT_CASE(3, true)
+    JC_RESIDENT_CASE(3, false)
+    JC_RESIDENT_CASE(4, false)
 #undef JC_RESIDENT_CASE
 #undef JC_RESIDENT_LAUNCH
     return hipErrorInvalidValue;
