@@ -45,6 +45,10 @@ inline constexpr int64_t resident_region_bytes(int64_t nx, int64_t ny, int64_t n
 // with a source 10.9 and 7.1.)
 constexpr int kResidentRegions[5] = {5120, 6656, 10240, 20480, 24832};
 
+// Blocks of up to this many planes have a build of their own, and its buffers.
+constexpr int kResidentFlatPlanes = 4;
+constexpr int kResidentFlatRegions[3] = {5120, 10240, 24832};
+
 // What a launch has to hold: the largest of each over the blocks it sweeps.
 struct ResidentShape {
     int pairs = 0, planes = 0;

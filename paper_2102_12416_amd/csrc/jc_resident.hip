@@ -43,6 +43,15 @@
 // Where a sweep turns, its first two steps' planes are written, a barrier, its
 // first neighbours are read, and another barrier protects them from the third
 // step's planes: steps + 1 barriers per sweep.
+//
+// Blocks of up to four planes (FLAT) have their own build, with registers for
+// four planes only.  Two steps have no third and need no such barrier; a single
+// step takes the two halves of the buffers in turn, one barrier per sweep.  (The
+// build for 32 planes has no registers left for these paths: with them 32^3 took
+// 15.0 us per sweep instead of 8.1.)  One block, us per sweep without / with a
+// source, in the build for 32 planes and here: 32 x 32 x 4 1.09 / 1.14 and 0.91 /
+// 0.93; 256 x 2 x 2 0.55 / 0.56 and 0.33 / 0.33; 1024 x 1 x 1 0.57 / 0.59 and
+// 0.32 / 0.32.
 
 #include <hip/hip_runtime.h>
 
@@ -80,13 +89,13 @@ struct Around {
     v2d ym[2], yp[2];
 };
 
-// ODD: some block swept has an odd nx.  STAGGER: see `early`.  R: bytes of a
-// plane buffer with its ghost rings.
-template <bool SRC, bool ODD, bool STAGGER, int R>
+// NZM: the most planes of a block.  ODD: some block swept has an odd nx.
+// STAGGER: see `early`.  R: bytes of a plane buffer with its ghost rings.
+template <int NZM, bool SRC, bool ODD, bool STAGGER, int R>
 __global__ void __launch_bounds__(kResidentMaxPairs)
 k_resident(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items, int parity, int nsweeps)
 {
-    constexpr int NZM = kResidentMaxPlanes;
+    constexpr bool FLAT = NZM <= kResidentFlatPlanes;
     constexpr int NBM = (NZM + 1) / 2;
     __shared__ v2d lds[4 * R / 16];
     const int blk = items ? items[blockIdx.x].block : 0;
@@ -111,6 +120,11 @@ k_resident(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items,
         double* const r = reinterpret_cast<double*>(base + (z & 3) * R + ring + (z >> 2) * slot + 32 * ep);
         r[y] = u[o];
         r[ny + y] = u[o + nx + 1];
+        if (FLAT && nb == 1) {                    // for the sweeps in the other two buffers
+            double* const q = r + 2 * R / 8;
+            q[y] = u[o];
+            q[ny + y] = u[o + nx + 1];
+        }
     }
     for (int i = t; i < nz * ep; i += blockDim.x) {
         const int z = i / ep, j = i % ep;
@@ -118,13 +132,19 @@ k_resident(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items,
         v2d* const r = reinterpret_cast<v2d*>(base + (z & 3) * R + ring + (z >> 2) * slot);
         r[j] = *(const v2d JC_GLOBAL*)(u + o);
         r[ep + j] = *(const v2d JC_GLOBAL*)(u + o + (int64_t)(ny + 1) * pitch);
+        if (FLAT && nb == 1) {
+            v2d* const q = r + 2 * R / 16;
+            q[j] = r[j];
+            q[ep + j] = r[ep + j];
+        }
     }
 
     // waves without a pair only keep the barriers company
     if (__builtin_amdgcn_readfirstlane(t & ~63) >= npair) {
         __syncthreads();
+        const int barriers = FLAT ? nb : nb + 1;      // per sweep
         for (int k = 0; k < nsweeps; ++k)
-            for (int i = 0; i <= nb; ++i)
+            for (int i = 0; i < barriers; ++i)
                 __syncthreads();
         return;
     }
@@ -185,10 +205,11 @@ k_resident(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items,
     }
     __syncthreads();                              // ghost rings written
 
-    // write the pairs of step I's planes (OFF: slot of plane p is p - OFF)
-    auto put = [&](auto ic, auto offc) __attribute__((always_inline)) {
+    // write the pairs of step I's planes (OFF: slot of plane p is p - OFF) into
+    // buffers (2 I + 2 HALF) mod 4 and the next
+    auto put = [&](auto ic, auto offc, auto halfc) __attribute__((always_inline)) {
         constexpr int I = decltype(ic)::value, OFF = decltype(offc)::value;
-        constexpr int Z = 2 * I + 1, B0 = ((2 * I) & 3) * (R / 16);
+        constexpr int Z = 2 * I + 1, B0 = ((2 * I + 2 * decltype(halfc)::value) & 3) * (R / 16);
         v2d w;
         w.x = ca[Z - OFF];
         w.y = cb[Z - OFF];
@@ -197,8 +218,8 @@ k_resident(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items,
         w.y = cb[Z + 1 - OFF];
         lds[t + B0 + R / 16] = w;
     };
-    auto get = [&](auto ic, Around& n) __attribute__((always_inline)) {
-        constexpr int I = decltype(ic)::value, B0 = ((2 * I) & 3) * R;
+    auto get = [&](auto ic, Around& n, auto halfc) __attribute__((always_inline)) {
+        constexpr int I = decltype(ic)::value, B0 = ((2 * I + 2 * decltype(halfc)::value) & 3) * R;
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             n.xm[k] = *reinterpret_cast<const double*>(base + r_xm + (B0 + k * R));
@@ -307,6 +328,9 @@ k_resident(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items,
     using Down = std::integral_constant<int, 1>;
     using No = std::false_type;
     using Yes = std::true_type;
+    using Low = std::integral_constant<int, 0>;
+    using High = std::integral_constant<int, 1>;
+    using First = std::integral_constant<int, 0>;
     Around around[2];                             // of step I in I & 1
     // nz, opaque to the compiler in every step: it would otherwise hold every
     // step's conditions in registers
@@ -329,10 +353,10 @@ k_resident(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items,
                 auto lds_work = [&]() __attribute__((always_inline)) {
                     if constexpr ((Next::value & 1) == 0)
                         ring_up();
-                    get(Next{}, around[(I + 1) & 1]);
+                    get(Next{}, around[(I + 1) & 1], Low{});
                     if constexpr (I + 2 < NBM) {
                         if (2 * I + 4 < top)
-                            put(Next2{}, Up{});
+                            put(Next2{}, Up{}, Low{});
                     }
                 };
                 if (early)
@@ -362,18 +386,19 @@ k_resident(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items,
             if constexpr (I >= 1) {
                 if constexpr ((I & 1) == 0)
                     ring_down();
-                get(Next{}, around[(I - 1) & 1]);
+                get(Next{}, around[(I - 1) & 1], Low{});
             }
             if constexpr (I >= 2)
-                put(Next2{}, Down{});
+                put(Next2{}, Down{}, Low{});
         };
         if (2 * I + 2 >= top) {                   // the sweep's first step
-            put(ic, Down{});
+            put(ic, Down{}, Low{});
             if constexpr (I >= 1)
-                put(Next{}, Down{});
+                put(Next{}, Down{}, Low{});
             __syncthreads();
-            get(ic, around[I & 1]);
-            __syncthreads();
+            get(ic, around[I & 1], Low{});
+            if constexpr (!FLAT)
+                __syncthreads();
             lds_work();
             update(ic, Down{}, Yes{}, top, around[I & 1]);
         } else {
@@ -388,16 +413,32 @@ k_resident(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items,
         if constexpr (I >= 1)
             __syncthreads();
     };
-    for (int k = 0; k < nsweeps; k += 2) {
-        put(std::integral_constant<int, 0>{}, Up{});
-        if (nb > 1)
-            put(std::integral_constant<int, 1>{}, Up{});
-        __syncthreads();
-        get(std::integral_constant<int, 0>{}, around[0]);
-        __syncthreads();
-        up_steps<0, NBM>(up);
-        if (k + 1 < nsweeps)
-            down_steps<NBM - 1>(down);
+    if (FLAT && nb == 1) {
+        for (int k = 0; k < nsweeps; k += 2) {
+            put(First{}, Up{}, Low{});
+            __syncthreads();
+            get(First{}, around[0], Low{});
+            update(First{}, Up{}, Yes{}, nz, around[0]);
+            if (k + 1 < nsweeps) {
+                put(First{}, Down{}, High{});
+                __syncthreads();
+                get(First{}, around[0], High{});
+                update(First{}, Down{}, Yes{}, nz, around[0]);
+            }
+        }
+    } else {
+        for (int k = 0; k < nsweeps; k += 2) {
+            put(First{}, Up{}, Low{});
+            if (FLAT || nb > 1)
+                put(std::integral_constant<int, 1>{}, Up{}, Low{});
+            __syncthreads();
+            get(First{}, around[0], Low{});
+            if constexpr (!FLAT)
+                __syncthreads();
+            up_steps<0, NBM>(up);
+            if (k + 1 < nsweeps)
+                down_steps<NBM - 1>(down);
+        }
     }
 
     double* const dst = B->u[p0 ^ (nsweeps & 1)];
@@ -426,28 +467,30 @@ hipError_t launch_resident(const BlockDesc* blocks, const Item* items, int nitem
     if (shape.pairs < 1 || shape.pairs > kResidentMaxPairs || shape.planes < 1 || shape.planes > kResidentMaxPlanes)
         return hipErrorInvalidValue;
     const dim3 grid(n), block((shape.pairs + 63) / 64 * 64);
-#define JC_RESIDENT_LAUNCH(SRC, ODD, STAGGER, K)                                                                \
-    hipLaunchKernelGGL((k_resident<SRC, ODD, STAGGER, kResidentRegions[K]>), grid, block, 0, s, blocks, items, parity, \
-                       nsweeps)
+#define JC_RESIDENT_LAUNCH(NZM, SRC, ODD, STAGGER, R)                                                            \
+    hipLaunchKernelGGL((k_resident<NZM, SRC, ODD, STAGGER, R>), grid, block, 0, s, blocks, items, parity, nsweeps)
     // the smallest buffers that hold every block: small blocks share a compute unit
-#define JC_RESIDENT_CASE(K, STAGGER)                                                                            \
-    if (shape.region <= kResidentRegions[K] && (!STAGGER || shape.pairs > 256)) {                                 \
+#define JC_RESIDENT_CASE(NZM, R, STAGGER)                                                                       \
+    if (shape.planes <= NZM && shape.region <= R && (!STAGGER || shape.pairs > 256)) {                            \
         if (src && shape.odd)                                                                                   \
-            JC_RESIDENT_LAUNCH(true, true, STAGGER, K);                                                          \
+            JC_RESIDENT_LAUNCH(NZM, true, true, STAGGER, R);                                                     \
         else if (src)                                                                                           \
-            JC_RESIDENT_LAUNCH(true, false, STAGGER, K);                                                         \
+            JC_RESIDENT_LAUNCH(NZM, true, false, STAGGER, R);                                                    \
         else if (shape.odd)                                                                                     \
-            JC_RESIDENT_LAUNCH(false, true, STAGGER, K);                                                         \
+            JC_RESIDENT_LAUNCH(NZM, false, true, STAGGER, R);                                                    \
         else                                                                                                    \
-            JC_RESIDENT_LAUNCH(false, false, STAGGER, K);                                                        \
+            JC_RESIDENT_LAUNCH(NZM, false, false, STAGGER, R);                                                   \
         return hipGetLastError();                                                                               \
     }
-    JC_RESIDENT_CASE(0, false)
-    JC_RESIDENT_CASE(1, false)
-    JC_RESIDENT_CASE(2, false)
-    JC_RESIDENT_CASE(3, true)
-    JC_RESIDENT_CASE(3, false)
-    JC_RESIDENT_CASE(4, false)
+    JC_RESIDENT_CASE(kResidentFlatPlanes, kResidentFlatRegions[0], false)
+    JC_RESIDENT_CASE(kResidentFlatPlanes, kResidentFlatRegions[1], false)
+    JC_RESIDENT_CASE(kResidentFlatPlanes, kResidentFlatRegions[2], false)
+    JC_RESIDENT_CASE(kResidentMaxPlanes, kResidentRegions[0], false)
+    JC_RESIDENT_CASE(kResidentMaxPlanes, kResidentRegions[1], false)
+    JC_RESIDENT_CASE(kResidentMaxPlanes, kResidentRegions[2], false)
+    JC_RESIDENT_CASE(kResidentMaxPlanes, kResidentRegions[3], true)
+    JC_RESIDENT_CASE(kResidentMaxPlanes, kResidentRegions[3], false)
+    JC_RESIDENT_CASE(kResidentMaxPlanes, kResidentRegions[4], false)
 #undef JC_RESIDENT_CASE
 #undef JC_RESIDENT_LAUNCH
     return hipErrorInvalidValue;

@@ -24,7 +24,10 @@ int main()
                 for (int r : jc::kResidentRegions)
                     if (!region && s.region <= r)
                         region = r;
-                if (!region) {
+                bool flat = nz > jc::kResidentFlatPlanes;
+                for (int r : jc::kResidentFlatRegions)
+                    flat = flat || s.region <= r;
+                if (!region || !flat) {
                     if (unfit++ < 10)
                         std::fprintf(stderr, "%d x %d x %d: %ld bytes, no buffer\n", nx, ny, nz, (long)s.region);
                     continue;
