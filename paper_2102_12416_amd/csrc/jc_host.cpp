@@ -238,9 +238,17 @@ void build_items(jc_ctx* c)
 // 160 16 x 32 32 against 47, 256^3 16 x 64 61 against 83, 512^3 16 x 512 423
 // against 443, and jc_autotune's own shapes at 512^3 and 512 x 768 x 1536.
 //
-// The bfloat16 correction moves few bytes per instruction and is bound by
-// issue, so from 2^23 cells on two work-groups share a compute unit where two
-// sweeps go into a launch (512^3: 16 x 256 177 us per sweep, 16 x 512 207).
+// Two sweeps of a binary32 or bfloat16 correction: two work-groups share a
+// compute unit, and a round of both takes 1.7 (binary32) or 1.4 (bfloat16) times
+// a round of one, so a launch that leaves some compute units with one or none
+// is charged for it.  Per sweep with the outer step, 613 grids of 10^6 to 6 10^7
+// cells: counted as rounds of one work-group, bfloat16 2 % slower than columns of
+// 8 planes (32 on large grids) and binary32 9 % faster, this way 13 % and 10 %
+// faster (bfloat16 555 x 160 x 87: 16 x 44 15.8 us, 16 x 8 12.3, 16 x 18 11.4).
+// Where half of a tile's lanes or more are idle, this holds for binary32 at 1.4,
+// and for the iterate without a source too (30 x 122 x 507: 16 x 16 6.3 us, 16 x 8
+// 5.4).  In binary64 else, and with three sweeps, a second work-group gives
+// nothing (rounds of two: 2 to 15 % slower).
 //
 // Three sweeps of a binary32 or bfloat16 correction go by quads of cells
 // (k_sweep3q, 64 cells by 32 rows) from 2^22 cells on, planes by the same rule.
@@ -251,20 +259,24 @@ void build_items(jc_ctx* c)
 // against 3.5).
 constexpr int64_t kQuadCells = (int64_t)1 << 22;
 
-// The planes that take the fewest rounds x steps.
-int multi_planes(int64_t depth_z, int64_t tiles, int64_t slots, int sweeps)
+// The planes that take the fewest rounds x steps.  pair: 0, or what a round of
+// two work-groups per compute unit takes over a round of one.
+int multi_planes(int64_t depth_z, int64_t tiles, int sweeps, double pair)
 {
     const int64_t nz = std::min<int64_t>(depth_z, 1 << 20);
+    const int64_t slots = pair > 0 ? 2 * kComputeUnits : kComputeUnits;
     double best = 0;
     int planes = 1;
     for (int64_t k = 1; k <= nz; ++k) {
         const int64_t zc = (nz + k - 1) / k;
-        const int64_t n = tiles * ((nz + zc - 1) / zc);
+        const int64_t n = tiles * ((nz + zc - 1) / zc), rest = n % slots;
         // short columns only while they are needed to fill one round
-        if (k > 1 && zc < kMinZChunk && n > slots)
+        if (k > 1 && zc < kTwoStepFloorZ && n > slots)
             break;
-        const int64_t rounds = (n + slots - 1) / slots;
-        const double cost = (double)rounds * (double)(zc + 2 * sweeps) * (rounds > 1 ? 1.15 : 1.0);
+        double rounds = (double)((n + slots - 1) / slots) * (n > slots ? 1.15 : 1.0);
+        if (pair > 0)
+            rounds = (double)(n / slots) * pair + (rest == 0 ? 0.0 : rest <= kComputeUnits ? 1.0 : pair);
+        const double cost = rounds * (double)(zc + 2 * sweeps);
         if (best == 0 || cost < best) {
             best = cost;
             planes = (int)zc;
@@ -277,12 +289,19 @@ void default_multi_shape(jc_ctx* c)
 {
     const HostBlock& b = c->blocks[0];
     const int64_t cells = b.n[0] * b.n[1] * b.n[2], tx = (b.n[0] + 63) / 64;
-    const bool issue_bound = c->opt.ir_enable && c->opt.ir_dtype == JC_BF16 && cells >= ((int64_t)1 << 23);
+    const int64_t tiles = tx * ((b.n[1] + kTwoStepRows - 1) / kTwoStepRows);
     c->t2_rows = kTwoStepRows;
-    c->t2_zc = multi_planes(b.n[2], tx * ((b.n[1] + c->t2_rows - 1) / c->t2_rows),
-                            (int64_t)kComputeUnits * (issue_bound ? 2 : 1), c->depth());
     if (quad_sweeps(c) && cells >= kQuadCells)
-        c->quad_zc = multi_planes(b.n[2], tx * ((b.n[1] + kQuadRows - 1) / kQuadRows), kComputeUnits, 3);
+        c->quad_zc = multi_planes(b.n[2], tx * ((b.n[1] + kQuadRows - 1) / kQuadRows), 3, 0);
+    // the shape of the two-sweep launches, where the three-sweep ones go by quads
+    const int sweeps = c->quad_zc > 0 ? 2 : c->depth();
+    const bool idle = 2 * b.n[0] * b.n[1] <= tiles * 64 * kTwoStepRows;     // half of the lanes
+    double pair = 0.0;
+    if (sweeps == 2 && narrow_storage(c))
+        pair = idle || c->opt.ir_dtype == JC_BF16 ? 1.4 : 1.7;
+    else if (sweeps == 2 && idle && !c->opt.ir_enable && !c->opt.with_source)
+        pair = 1.4;
+    c->t2_zc = multi_planes(b.n[2], tiles, sweeps, pair);
     c->t2_auto = true;
 }
 

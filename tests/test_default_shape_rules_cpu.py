@@ -1,0 +1,49 @@
+"""Default launch shapes on grids where a rule once picked a slower one than the
+rule before it (host only, no device)."""
+import ctypes
+
+import pytest
+
+from paper_2102_12416_amd import _lib as L
+
+
+def check(st):
+    assert st == 0, L.last_error()
+
+
+def create(n, block=None, ir=None, **kw):
+    opt = L.Options()
+    opt.mode = 1
+    opt.ir_dtype = L.JC_NONE if ir is None else ir
+    opt.ir_enable = int(ir is not None)
+    opt.with_source = int(ir is not None)
+    for k, v in kw.items():
+        setattr(opt, k, v)
+    ctx = ctypes.c_void_p()
+    check(L.lib.jc_create(L.i64(n), L.i64(block or n), ctypes.byref(opt), ctypes.byref(ctx)))
+    return ctx
+
+
+def multi_shape(n, **kw):
+    ctx = create(n, temporal=1, **kw)
+    out = (ctypes.c_int64 * 3)()
+    check(L.lib.jc_temporal_info(ctx, out))
+    L.lib.jc_destroy(ctx)
+    return list(out)[1:]
+
+
+@pytest.mark.parametrize("n", [(555, 160, 87), (150, 467, 55), (369, 24, 317), (348, 54, 334), (131, 358, 173)])
+def test_two_sweeps_of_a_narrow_correction_fill_the_chip_twice(n):
+    """More work-groups than compute units: two share one."""
+    rows, planes = multi_shape(n, ir=L.JC_BF16)
+    assert rows == 16
+    groups = -(-n[0] // 64) * -(-n[1] // rows) * -(-n[2] // planes)
+    assert 256 < groups <= 512, (planes, groups)
+
+
+@pytest.mark.parametrize("n,source,depth,most", [((30, 122, 507), 0, 2, 12), ((31, 191, 333), 0, 2, 12),
+                                                 ((597, 424, 24), 1, 3, 12), ((631, 428, 28), 0, 2, 14)])
+def test_columns_where_one_round_of_long_ones_is_slower(n, source, depth, most):
+    """Half-idle tiles without a source, and thin grids of a round and a bit."""
+    rows, planes = multi_shape(n, with_source=source, sweeps_per_launch=depth)
+    assert rows == 16 and planes <= most, planes
