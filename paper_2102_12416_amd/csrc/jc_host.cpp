@@ -105,8 +105,16 @@ void region_tiles(const jc_ctx* c, int* tx, int* ty, int* zc)
 //    and the longest columns that allows: few halo planes, and neighbours
 //    march together, so shared halo rows hit in L2 (256^3: 16 x 64 50 us,
 //    8 x 16 64; 512^3: 16 x 512 368 us, 8 x 64 433).  Taken where at most 15 %
-//    of the round idles (several blocks: 5 %); bfloat16 is bound by issue and
-//    gains nothing.
+//    of the round idles (several blocks: 5 %), and where the taller tiles do not
+//    lose in idle lanes what the round gains: they cover at most 1/4 more than
+//    the region's tile does (binary32, bound more by issue: 1/20; 342 x 50 x 122:
+//    16 x 13 10.6 us, 8 x 16 8.2), and not less than 0.7 of their lanes are
+//    cells where the region's tiles run in at most 1.5 rounds themselves (45 x
+//    211 x 203: 16 x 12 9.4 us, 8 x 13 7.8).  Work-groups of 2 waves only in
+//    binary64 (binary32, 193 x 347 x 343: 4 x 172 85 us, 8 x 22 71).  Over 685
+//    grids of 10^6 to 8 10^7 cells the round then gains 7.2 % in binary64 and 2.4
+//    % in binary32, and 10 lose more than 3 % (without these limits 6.9 and 1.6
+//    %, and 76).  bfloat16 is bound by issue and gains nothing.
 //  - Otherwise many rounds of short work-groups, 8 rows by at most 12 planes
 //    (bfloat16: 16), whose tail is short (the uneven blocks above: 8 x 63
 //    planes 321 us with 32 cells, 247 with 32 x 8 x 11).
@@ -126,6 +134,9 @@ void default_tiles(const jc_ctx* c, int64_t max_items, int* tx, int* ty, int* zc
     }
     maxz = std::min<int64_t>(maxz, 1 << 20);
     const bool bf = c->opt.ir_enable && c->opt.ir_dtype == JC_BF16;
+    const bool f32 = c->opt.ir_enable && c->opt.ir_dtype == JC_F32;
+    int rx, ry, rz;
+    region_tiles(c, &rx, &ry, &rz);
     const bool narrow = (idle_cells(c, 64) - idle_cells(c, 32)) * 100 > cells * (bf ? 40 : 18) || maxx <= 32;
     const int x = narrow ? 32 : 64;
     const bool small = cells <= ((int64_t)1 << 20);
@@ -142,6 +153,8 @@ void default_tiles(const jc_ctx* c, int64_t max_items, int* tx, int* ty, int* zc
     for (int i = 0; i < nshapes; ++i) {
         const int64_t cap = (int64_t)kComputeUnits * shapes[i].per_cu;
         const bool long_only = i >= 2;            // 2- and 16-wave work-groups: for long columns
+        if (f32 && x / 2 * shapes[i].rows == 128)
+            continue;
         int pick = 0;
         for (int64_t k = 1; k <= maxz; ++k) {
             const int64_t z = (maxz + k - 1) / k;
@@ -171,15 +184,26 @@ void default_tiles(const jc_ctx* c, int64_t max_items, int* tx, int* ty, int* zc
         *zc = planes;
         return;
     }
-    const bool round = rows && planes >= 12 && !bf &&
-                       (c->nb() == 1 ? balance >= 0.85 : equal && planes >= 64 && balance >= 0.95);
+    bool round = rows && planes >= 12 && !bf &&
+                 (c->nb() == 1 ? balance >= 0.85 : equal && planes >= 64 && balance >= 0.95);
+    if (round) {
+        const double covered = (double)items_for(c, x, rows, 1) * x * rows;
+        const double region = (double)items_for(c, rx, ry, 1) * rx * ry;
+        const int64_t region_round = (int64_t)kComputeUnits * 8 * 64 / (rx / 2 * ry);
+        round = covered <= region * (f32 ? 1.05 : 1.25) &&
+                ((double)cells >= 0.7 * covered || 2 * items_for(c, rx, ry, rz) > 3 * region_round);
+    }
     if (round) {
         *ty = rows;
         *zc = planes;
         return;
     }
-    if ((rows && planes < 12) || cells <= (int64_t)1 << 24)
-        return region_tiles(c, tx, ty, zc);
+    if ((rows && planes < 12) || cells <= (int64_t)1 << 24) {
+        *tx = rx;
+        *ty = ry;
+        *zc = rz;
+        return;
+    }
     const int64_t most = bf ? 16 : 12;
     int64_t z = (maxz + (maxz + most - 1) / most - 1) / ((maxz + most - 1) / most);
     while (items_for(c, x, 8, (int)z) > max_items)

@@ -47,3 +47,25 @@ def test_columns_where_one_round_of_long_ones_is_slower(n, source, depth, most):
     """Half-idle tiles without a source, and thin grids of a round and a bit."""
     rows, planes = multi_shape(n, with_source=source, sweeps_per_launch=depth)
     assert rows == 16 and planes <= most, planes
+
+
+def tile(n, **kw):
+    ctx = create(n, **kw)
+    out = (ctypes.c_int64 * 4)()
+    check(L.lib.jc_tile_info(ctx, out))
+    L.lib.jc_destroy(ctx)
+    return list(out)[:3]
+
+
+@pytest.mark.parametrize("n,ir", [((342, 50, 122), None), ((149, 44, 338), None), ((45, 211, 203), None),
+                                  ((597, 18, 376), L.JC_F32), ((74, 36, 634), L.JC_F64), ((131, 46, 287), L.JC_F32),
+                                  ((193, 347, 343), L.JC_F32)])
+def test_no_round_of_tall_tiles_where_their_lanes_idle(n, ir):
+    assert tile(n, ir=ir)[1] == 8
+
+
+@pytest.mark.parametrize("n,ir,rows", [((256, 256, 256), None, 16), ((512, 512, 512), None, 16),
+                                       ((384, 320, 448), L.JC_F32, 16), ((285, 592, 67), None, 4)])
+def test_one_round_of_long_columns_is_kept(n, ir, rows):
+    t = tile(n, ir=ir)
+    assert t[1] == rows and t[2] >= 64, t
