@@ -117,7 +117,10 @@ void region_tiles(const jc_ctx* c, int* tx, int* ty, int* zc)
 //    %, and 76).  bfloat16 is bound by issue and gains nothing.
 //  - Otherwise many rounds of short work-groups, 8 rows by at most 12 planes
 //    (bfloat16: 16), whose tail is short (the uneven blocks above: 8 x 63
-//    planes 321 us with 32 cells, 247 with 32 x 8 x 11).
+//    planes 321 us with 32 cells, 247 with 32 x 8 x 11).  Not where the region's
+//    chunks have less than 18 planes already: these run as well, and the change of
+//    either size costs up to 6 % (106 x 624 x 274 in blocks of 106 x 123 x 84: 8 x
+//    12 70.5 us, 8 x 11 66.6; 238 x 181 x 553 uneven: 32 x 8 x 12 96.6, x 17 92.7).
 //  Between these -- up to the size where a round's columns reach 12 planes,
 //  and where many rounds are left up to 2^24 cells -- nothing beats the
 //  region's own tile by more than its spread.
@@ -198,7 +201,7 @@ void default_tiles(const jc_ctx* c, int64_t max_items, int* tx, int* ty, int* zc
         *zc = planes;
         return;
     }
-    if ((rows && planes < 12) || cells <= (int64_t)1 << 24) {
+    if ((rows && planes < 12) || cells <= (int64_t)1 << 24 || rz < 18) {
         *tx = rx;
         *ty = ry;
         *zc = rz;

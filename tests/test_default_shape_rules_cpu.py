@@ -69,3 +69,13 @@ def test_no_round_of_tall_tiles_where_their_lanes_idle(n, ir):
 def test_one_round_of_long_columns_is_kept(n, ir, rows):
     t = tile(n, ir=ir)
     assert t[1] == rows and t[2] >= 64, t
+
+
+@pytest.mark.parametrize("n,block,planes", [((106, 624, 274), (106, 123, 84), 11), ((342, 402, 175), (226, 184, 175), 11),
+                                            ((579, 576, 78), None, 10)])
+def test_short_chunks_are_left_as_they_are(n, block, planes):
+    assert tile(n, block=block) == [64, 8, planes]
+
+
+def test_long_chunks_of_many_blocks_become_short():
+    assert tile((371, 402, 310), block=(53, 159, 99)) == [64, 8, 11]
