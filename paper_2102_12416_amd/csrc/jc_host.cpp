@@ -1666,8 +1666,10 @@ int jc_solve(jc_ctx* c, double rtol, int64_t max_iter, int64_t check_every, jc_s
             if (st != JC_OK)
                 return st;
             r = std::sqrt(s);
-            if (!std::isfinite(r))
+            if (!std::isfinite(r)) {
+                JC_HIP(hipStreamSynchronize(c->stream));
                 return fail(JC_ERR_NONFINITE, "residual is not finite at iteration " + std::to_string(start + k));
+            }
             if (r0 < 0)
                 r0 = r;
             record(r);
@@ -1757,8 +1759,10 @@ int jc_solve_ir(jc_ctx* c, int inner_sweeps, double rtol, int64_t max_inner, jc_
         if (st != JC_OK)
             return st;
         r = std::sqrt(ss);
-        if (!std::isfinite(r))
+        if (!std::isfinite(r)) {
+            JC_HIP(hipStreamSynchronize(c->stream));
             return fail(JC_ERR_NONFINITE, "residual is not finite after " + std::to_string(done) + " inner sweeps");
+        }
         if (r0 < 0)
             r0 = r;
         if (info->history && info->history_len < info->history_cap)
