@@ -422,9 +422,12 @@ int jc_temporal_info(const jc_ctx* ctx, int64_t out[3]);
 /* Time `reps` sweeps of every valid candidate shape (tile_x in {64, 32,
  * 16}, and 96, 128 or 256 where the storage is binary64 and they leave at
  * most 1/8 of the lanes idle, x tile_y in {4, 8, 16, 32} x z_chunk in {16,
- * 32, 64, ..., depth}) on
+ * 32, 64, ..., depth}) and of the shape the context has on
  * the bound stream after at least 150 ms of warm-up sweeps, time the four
  * fastest again in turn over three rounds and keep the fastest of those;
+ * the shape the context has stays unless another is 2 % faster (on a
+ * decomposed grid of up to 2^20 cells only the candidates are timed, so
+ * z_chunk there becomes at least 16).
  * out = {tile_x, tile_y, z_chunk, microseconds per sweep}.  The sweep timed
  * is the one the context's solve loop runs: the plain sweep, or, on a
  * context with refinement buffers (ir_enable), the inner sweep of the
@@ -434,12 +437,13 @@ int jc_temporal_info(const jc_ctx* ctx, int64_t out[3]);
  * the correction, on a context with refinement buffers) is then timed over
  * rows {8, 16, 24} x z chunks of 1/1 .. 1/16 of the depth and the shape it
  * has, which stays unless another is 2 % faster (max(reps, 2) launches
- * each, the three fastest again over three rounds), and the fastest kept (jc_temporal_info); the one shape serves both two-sweep
- * launches of the context.  The pace of the one-sweep launch is tuned for
- * the chosen shape (jc_autotune_pace); out[3] is then the time with it.  The trial sweeps write only
- * the other ping-pong copy and face slot, so the current iterate and
- * iteration count are unchanged.  Waits for the stream.  Needs a loaded
- * context. */
+ * each, the three fastest again over three rounds), and the fastest kept
+ * (jc_temporal_info); the one shape serves both two-sweep launches of the
+ * context.  The pace of the one-sweep launch is tuned for
+ * the chosen shape (jc_autotune_pace); out[3] is then the time with it.
+ * The trial sweeps write only the other ping-pong copy and face slot, so
+ * the current iterate and iteration count are unchanged.  Waits for the
+ * stream.  Needs a loaded context. */
 int jc_autotune(jc_ctx* ctx, int reps, int64_t out[4]);
 
 /* Pace of the launch the context's solve loop runs: the one-sweep launch
