@@ -403,17 +403,20 @@ int jc_set_tiles(jc_ctx* ctx, int tile_x, int tile_y, int z_chunk);
 
 /* Shape of the multi-sweep launch of temporal blocking: rows of its tile
  * (8, 16 or 24 for two sweeps per launch, 8 or 16 for three; the tile is 64
- * cells wide) and planes per work-group (>= 1).
+ * cells wide) and planes per work-group (>= 1).  32 rows, for three sweeps of
+ * a binary32 or bfloat16 correction: its launches by quads of cells, beside
+ * which the two-sweep launches keep their shape.
  * Results are bitwise independent of it.  JC_ERR_STATE unless the context
  * was created with temporal = 1. */
 int jc_set_temporal_tiles(jc_ctx* ctx, int rows, int z_chunk);
 /* out = {sweeps per launch (2 or 3; 0 without temporal blocking), rows,
- * planes per work-group} of the multi-sweep launch.  Until set
- * (jc_set_temporal_tiles or jc_autotune), the shape is the library's default
- * for the grid (16 rows); three sweeps of a large binary32 or bfloat16
- * correction then run in tiles of 64 cells by 32 rows with planes of their
- * own, as they do where jc_autotune finds that faster, and this is the shape
- * of the two-sweep launches beside them.  With a z_chunk given at creation or
+ * planes per work-group} of the multi-sweep launch, as it was set
+ * (jc_set_temporal_tiles) or tuned (jc_autotune); to set it on a context of
+ * the same grid and options gives the same launches.  Until then it is the
+ * library's default for the grid (16 rows), beside which three sweeps of a
+ * correction of 2^22 cells or more in binary32 or bfloat16 run in tiles of 64
+ * cells by 32 rows with planes of their own; to set what a default reports
+ * changes nothing.  With a z_chunk given at creation or
  * by jc_set_tiles it is 16 rows and the planes follow z_chunk, at least 32,
  * halved (down to 8) while a launch would have fewer than 1024
  * work-groups. */
@@ -435,7 +438,8 @@ int jc_temporal_info(const jc_ctx* ctx, int64_t out[3]);
  * step rebuilds them; JC_ERR_STATE while a group's refinement step is in
  * progress on the context).  With temporal = 1 the two-sweep launch (of
  * the correction, on a context with refinement buffers) is then timed over
- * rows {8, 16, 24} x z chunks of 1/1 .. 1/16 of the depth and the shape it
+ * rows {8, 16, 24} (three sweeps: 8 and 16, of a binary32 or bfloat16
+ * correction 32 too) x z chunks of 1/1 .. 1/16 of the depth and the shape it
  * has, which stays unless another is 2 % faster (max(reps, 2) launches
  * each, the three fastest again over three rounds), and the fastest kept
  * (jc_temporal_info); the one shape serves both two-sweep launches of the

@@ -144,6 +144,7 @@ struct jc_ctx {
     // three sweeps per launch by quads of cells (binary32 / bfloat16
     // correction): planes per work-group, 0 = by pairs in the shape above
     int quad_zc = 0;
+    bool quad_set = false;          // by jc_autotune or jc_set_temporal_tiles, not the default rule
     bool t2_auto = false;           // the shape is default_multi_shape's
     // pace of the one-sweep launches of the solve loop (jc_set_pace): ticks
     // of the 100 MHz constant clock per plane step; 0 = none

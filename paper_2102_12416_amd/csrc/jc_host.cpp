@@ -1254,7 +1254,8 @@ int tune_two_step(jc_ctx* c, int reps, MultiShape had)
     for (const Cand& k : cand)
         if (is_had(k) && k.ms <= best.ms * kTuneMargin)
             best = k;
-    if (best.rows == jc_rt::kQuadRows) {
+    c->quad_set = best.rows == jc_rt::kQuadRows;
+    if (c->quad_set) {
         c->quad_zc = best.zc;              // the two-sweep launches keep their shape
         c->t2_zc = two_step_chunk(c);
     } else {
@@ -1897,14 +1898,24 @@ int jc_set_temporal_tiles(jc_ctx* c, int rows, int z_chunk)
         return fail(JC_ERR_INVALID, "NULL context");
     if (!c->opt.temporal)
         return fail(JC_ERR_STATE, "the context was created without temporal blocking");
-    if (c->depth() == 3 ? !jc_rt::three_step_rows_ok(rows) : !jc_rt::two_step_rows_ok(rows))
-        return fail(JC_ERR_INVALID, c->depth() == 3 ? "rows must be 8 or 16 (three sweeps per launch)"
+    const bool quads = rows == jc_rt::kQuadRows && jc_rt::quad_sweeps(c);
+    if (!quads && (c->depth() == 3 ? !jc_rt::three_step_rows_ok(rows) : !jc_rt::two_step_rows_ok(rows)))
+        return fail(JC_ERR_INVALID, c->depth() == 3 ? "rows must be 8 or 16 (three sweeps per launch; of a binary32 "
+                                                      "or bfloat16 correction also 32)"
                                                     : "rows must be 8, 16 or 24");
     if (z_chunk < 1)
         return fail(JC_ERR_INVALID, "z_chunk must be >= 1");
-    c->t2_rows = rows;
-    c->t2_zc = z_chunk;
-    c->quad_zc = 0;
+    if (quads) {
+        c->t2_zc = two_step_chunk(c);      // the two-sweep launches keep their shape
+        c->quad_zc = z_chunk;
+        c->quad_set = true;
+    } else if (!(c->t2_auto && rows == c->t2_rows && z_chunk == two_step_chunk(c))) {
+        // (the shape that a default reports keeps the launches that it has)
+        c->t2_rows = rows;
+        c->t2_zc = z_chunk;
+        c->quad_zc = 0;
+        c->quad_set = false;
+    }
     c->t2_auto = false;
     c->pace = 0;                           // a pace belongs to a shape
     free_graphs(c);                        // graphs hold the old launch shapes
@@ -1916,8 +1927,8 @@ int jc_temporal_info(const jc_ctx* c, int64_t out[3])
     if (!c || !out)
         return fail(JC_ERR_INVALID, "NULL argument");
     out[0] = c->opt.temporal ? c->depth() : 0;
-    out[1] = c->t2_rows;
-    out[2] = two_step_chunk(c);
+    out[1] = c->quad_set && c->quad_zc > 0 ? jc_rt::kQuadRows : c->t2_rows;
+    out[2] = c->quad_set && c->quad_zc > 0 ? c->quad_zc : two_step_chunk(c);
     return JC_OK;
 }
 
