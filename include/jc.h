@@ -282,8 +282,9 @@ int jc_solve_ir(jc_ctx* ctx, int inner_sweeps, double rtol, int64_t max_inner,
  * inner sweeps; a refining member must hold its iterate in copy 0.
  * ctxs is read during the call; the contexts must outlive the group and
  * must not be used on their own streams while the group exists.
- * flags: bit 0 = capture jc_group_iterate windows as HIP graphs (needs a
- * non-null stream); bit 1 = two sweeps of every member per launch
+ * flags: bit 0 = capture jc_group_iterate windows of 8 launches or more as
+ * HIP graphs (needs a non-null stream; not with bit 3, whose windows are one
+ * launch per class); bit 1 = two sweeps of every member per launch
  * (temporal blocking; every member one block, else JC_ERR_INVALID; tiles
  * of 64 cells x 16 rows x max(planes, 32) with a tile given, else of planes
  * (and, for three binary32 or bfloat16 sweeps, cells x rows) that suit the

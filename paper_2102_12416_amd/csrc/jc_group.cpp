@@ -701,10 +701,10 @@ int jc_group_iterate(jc_group* g, int64_t n)
     const int64_t rest = n - done;
     if (rest <= 0)
         return JC_OK;
-    int64_t launches = 0;                         // of the rest of the window
-    for (size_t i = 0; i < g->classes.size(); ++i)
-        launches += g->resident ? 1 : g->three_step ? rest / 3 + (rest % 3 != 0) : g->two_step ? (rest + 1) / 2 : rest;
-    if (!g->use_graphs || launches < kGraphMinLaunches)
+    // launches of the rest of the window (a resident group's: one per class, of
+    // which there are two at most)
+    const int64_t each = g->three_step ? rest / 3 + (rest % 3 != 0) : g->two_step ? (rest + 1) / 2 : rest;
+    if (!g->use_graphs || g->resident || each * (int64_t)g->classes.size() < kGraphMinLaunches)
         return group_run(g, rest);
     // graph of `rest` sweeps from the current launch parity; the d copy
     // of refinement members alternates with the launch parity
