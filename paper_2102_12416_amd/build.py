@@ -59,5 +59,18 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
+def build_device_check(verbose: bool = False) -> str:
+    """Compile the tests' device checks of the shared helpers."""
+    tests = os.path.join(ROOT, "tests")
+    lib = os.path.join(tests, "libdevice_check.so")
+    tmp = lib + ".tmp%d" % os.getpid()
+    cmd = [hipcc()] + FLAGS + ["-shared", "-I", CSRC, "-o", tmp, os.path.join(tests, "device_check.hip")]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(tmp, lib)
+    return lib
+
+
 if __name__ == "__main__":
     print(build(verbose="-v" in sys.argv))

@@ -28,7 +28,8 @@ __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w 
 // of gfx950: one instruction for ten (shift, bit field, add and NaN select of
 // each value).  Compared with the shift form -- add 0x7fff plus the kept
 // half's lowest bit, NaN kept quiet -- over all 2^32 binary32 patterns in
-// both halves: the same bits, denormals and NaN included.
+// both halves: the same bits, denormals and NaN included
+// (tests/device_check.hip).
 __device__ __forceinline__ uint32_t bf16_pair(float a, float b)
 {
     typedef __bf16 v2b __attribute__((ext_vector_type(2)));
