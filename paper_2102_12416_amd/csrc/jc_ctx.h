@@ -164,7 +164,7 @@ struct jc_ctx {
     int64_t max_items = 0;
     // arena layout
     size_t off_blocks = 0, off_pairs = 0, off_items = 0, off_partials = 0, off_ranges = 0,
-           off_result = 0, footprint = 0;
+           footprint = 0;
     size_t lo_begin = 0, lo_end = 0;   // refinement arrays and buffers
     size_t lxg_off = 0;                 // zero ghost column of the correction (in the refinement region)
     // binding

@@ -5,9 +5,11 @@
 // kernel class (plain binary64 with or without a source; refinement by
 // storage format and source).  Every launch covers all members of a
 // class; each work item carries its member's ping-pong flip, so members
-// admitted at different times stay independent.  The tile shape is fixed
-// for a group (it never depends on who else is in it), so a member's
-// results and residual norms are bitwise the same alone and in any mix.
+// admitted at different times stay independent.  The one-sweep tile, which
+// the residual norms' partial sums follow, is fixed for a group (it never
+// depends on who else is in it), so a member's results and residual norms are
+// bitwise the same alone and in any mix.  The tiles of multi-sweep launches
+// (multi_shape) do follow the members' sizes; no result depends on them.
 
 #include <hip/hip_runtime.h>
 
@@ -154,7 +156,7 @@ int prime_faces(jc_group* g)
 // unit): 24 of edge 96 48 -> 41 us, 48 of edge 64 32 -> 26, 12 of edge 128 53 ->
 // 45, 48 of edge 96 93 -> 91.  In one round pairs are faster (8 of edge 96 20.7
 // against 24.5, 56 of edge 32 9.8 against 11.4), and bfloat16 gains and loses (48
-// of edge 64 38 -> 28, of edge 96 73 -> 94).
+// of edge 64 38 -> 28, of edge 96 77 -> 94).
 //
 // A given tile keeps 64 x 16 cells by its z chunk, at least kTwoStepMinZ; so
 // does a class of more than kMultiSearchItems such tiles, whose rounds are many

@@ -486,7 +486,6 @@ int build_geometry(jc_ctx* c, const int64_t grid[3], const std::vector<int64_t> 
     c->off_items = off; off = align_up(off + sizeof(Item) * (size_t)c->max_items, kAlign);
     c->off_partials = off; off = align_up(off + sizeof(double) * (size_t)c->max_items, kAlign);
     c->off_ranges = off; off = align_up(off + sizeof(int32_t) * 2, kAlign);
-    c->off_result = off; off = align_up(off + sizeof(double) * 4, kAlign);
     for (HostBlock& b : c->blocks) {
         // element (0,0,0) sits 15 elements into a 128-byte line so that
         // cell x = 1 of every row starts a line; 16 elements of slack

@@ -326,7 +326,7 @@ k_sweep2(OneBlock one, const BlockDesc* __restrict__ blocks, const Item* __restr
 // over pairs 1 .. TXP + 2), then the third ring (the outermost rows, then
 // pairs 0 and TXP + 3 of the other rows), whose iterate k + 1 is not
 // needed.  Work as for k_sweep2 (items null: the
-// tiles of blocks[0]; else a work list of 2 TXP x TY tiles).
+// tiles of `one`; else a work list of 2 TXP x TY tiles).
 template <typename T, int FIELD, int TXP, int TY, bool SRC>
 __global__ void __launch_bounds__(((TXP + 4) * (TY + 6) + 63) / 64 * 64)
 k_sweep3(OneBlock one, const BlockDesc* __restrict__ blocks, const Item* __restrict__ items, int parity, int ntiles,
@@ -898,7 +898,8 @@ hipError_t sweep2_rows(const OneBlock& one, const BlockDesc* blocks, const Item*
     case 16: return sweep2_launch<T, FIELD, 32, 16, SRC>(one, blocks, items, parity, n, s, pace);
     case 24: return sweep2_launch<T, FIELD, 32, 24, SRC>(one, blocks, items, parity, n, s, pace);
     case 32:
-        // a work list of 32-cell tiles
+        // a work list of 32-cell tiles: the last two sweeps of a window that a
+        // group sweeps three at a time
         if constexpr (sizeof(T) < 8)
             return items ? sweep2_launch<T, FIELD, 16, 32, SRC>(one, blocks, items, parity, n, s, pace)
                          : hipErrorInvalidValue;
