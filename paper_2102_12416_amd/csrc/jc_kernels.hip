@@ -281,6 +281,9 @@ k_sweep(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items, in
             const C r_b = SRC ? (s_b + sb) - six * c_b : sb - six * c_b;
             acc = acc + (a_ok ? (double)(r_a * r_a) : 0.0);
             acc = acc + (b_ok ? (double)(r_b * r_b) : 0.0);
+            // summed here: the compiler would put the sums of all unrolled
+            // planes off to the last of them, and hold or spill their terms
+            asm("" : "+v"(acc));
             if constexpr (RLO) {
                 // r rounded to the refinement's storage, through binary32
                 R* o = static_cast<R*>(B->rlo) + (int64_t)z * B->lplane + (int64_t)y * B->lpitch + xa;
