@@ -218,24 +218,24 @@ void default_tiles(const jc_ctx* c, int64_t max_items, int* tx, int* ty, int* zc
 void build_items(jc_ctx* c)
 {
     c->items.clear();
+    c->items.reserve((size_t)items_for(c, c->tile_x, c->tile_y, c->z_chunk));
     for (int bi = 0; bi < c->nb(); ++bi) {
         const HostBlock& b = c->blocks[bi];
         const int64_t nch = (b.n[2] + c->z_chunk - 1) / c->z_chunk;
-        for (int64_t k = 0; k < nch; ++k)
+        Item it{};
+        it.block = bi;
+        for (int64_t k = 0; k < nch; ++k) {
+            int64_t z0 = 0, zlen = 0;
+            z_chunk_range(b.n[2], c->z_chunk, k, &z0, &zlen);
+            it.z0 = (int32_t)z0;
+            it.zlen = (int32_t)zlen;
             for (int64_t y0 = 0; y0 < b.n[1]; y0 += c->tile_y)
                 for (int64_t x0 = 0; x0 < b.n[0]; x0 += c->tile_x) {
-                    int64_t z0 = 0, zlen = 0;
-                    z_chunk_range(b.n[2], c->z_chunk, k, &z0, &zlen);
-                    Item it{};
-                    it.block = bi;
                     it.x0 = (int32_t)x0;
                     it.y0 = (int32_t)y0;
-                    it.z0 = (int32_t)z0;
-                    it.zlen = (int32_t)zlen;
-                    it.flip = 0;
-                    it.owner = 0;
                     c->items.push_back(it);
                 }
+        }
     }
     // boundary-first iterations: the tiles holding a cell of a paired face
     // plane go first (their sweep writes every face value of the new
@@ -375,7 +375,8 @@ int validate_options(const jc_options* opt)
     return JC_OK;
 }
 
-int build_geometry(jc_ctx* c, const int64_t grid[3], const std::vector<int64_t> cuts[3],
+// tables: with the launch shapes and the work list, which no footprint needs.
+int build_geometry(jc_ctx* c, bool tables, const int64_t grid[3], const std::vector<int64_t> cuts[3],
                    const jc_options* opt)
 {
     int st = validate_options(opt);
@@ -471,14 +472,16 @@ int build_geometry(jc_ctx* c, const int64_t grid[3], const std::vector<int64_t> 
     region_tiles(c, &c->tile_x, &c->tile_y, &c->z_chunk);
     c->max_items = std::max<int64_t>({items_for(c, c->tile_x, c->tile_y, c->z_chunk), items_for(c, 32, 4, kMinZChunk),
                                       items_for(c, 16, 8, kMinZChunk)});
-    // boundary-first iterations need tiles away from the faces: as before
-    if (c->opt.tile_x <= 0 && c->opt.tile_y <= 0 && c->opt.z_chunk <= 0 && !c->opt.overlap)
-        default_tiles(c, c->max_items, &c->tile_x, &c->tile_y, &c->z_chunk);
-    build_items(c);
-    if (c->opt.temporal && c->opt.z_chunk <= 0)
-        default_multi_shape(c);
     if (c->max_items > (int64_t)1 << 30)
         return fail(JC_ERR_INVALID, "work list too long");
+    if (tables) {
+        // boundary-first iterations need tiles away from the faces: as before
+        if (c->opt.tile_x <= 0 && c->opt.tile_y <= 0 && c->opt.z_chunk <= 0 && !c->opt.overlap)
+            default_tiles(c, c->max_items, &c->tile_x, &c->tile_y, &c->z_chunk);
+        build_items(c);
+        if (c->opt.temporal && c->opt.z_chunk <= 0)
+            default_multi_shape(c);
+    }
     // arena layout
     size_t off = 0;
     c->off_blocks = off; off = align_up(off + sizeof(BlockDesc) * c->blocks.size(), kAlign);
@@ -546,7 +549,7 @@ std::vector<int64_t> uniform_cuts(int64_t n, int64_t bd)
     return v;
 }
 
-int uniform_geometry(jc_ctx* c, const int64_t grid[3], const int64_t block_dims[3], const jc_options* opt)
+int uniform_geometry(jc_ctx* c, bool tables, const int64_t grid[3], const int64_t block_dims[3], const jc_options* opt)
 {
     if (!grid || !block_dims)
         return fail(JC_ERR_INVALID, "grid and block_dims must not be NULL");
@@ -560,10 +563,10 @@ int uniform_geometry(jc_ctx* c, const int64_t grid[3], const int64_t block_dims[
             return fail(JC_ERR_INVALID, "too many blocks along an axis");
         cuts[a] = uniform_cuts(grid[a], block_dims[a]);
     }
-    return build_geometry(c, grid, cuts, opt);
+    return build_geometry(c, tables, grid, cuts, opt);
 }
 
-int rect_geometry(jc_ctx* c, const int64_t grid[3], const int64_t* const cuts[3], const int64_t ncuts[3],
+int rect_geometry(jc_ctx* c, bool tables, const int64_t grid[3], const int64_t* const cuts[3], const int64_t ncuts[3],
                   const jc_options* opt)
 {
     if (!grid || !cuts || !ncuts)
@@ -574,7 +577,7 @@ int rect_geometry(jc_ctx* c, const int64_t grid[3], const int64_t* const cuts[3]
             return fail(JC_ERR_INVALID, "each axis needs 1..65535 block edges");
         v[a].assign(cuts[a], cuts[a] + ncuts[a]);
     }
-    return build_geometry(c, grid, v, opt);
+    return build_geometry(c, tables, grid, v, opt);
 }
 
 }  // namespace
@@ -1316,7 +1319,7 @@ int jc_footprint(const int64_t grid[3], const int64_t block_dims[3], const jc_op
     if (!bytes)
         return fail(JC_ERR_INVALID, "bytes must not be NULL");
     jc_ctx tmp;
-    int st = uniform_geometry(&tmp, grid, block_dims, opt);
+    int st = uniform_geometry(&tmp, false, grid, block_dims, opt);
     if (st != JC_OK)
         return st;
     *bytes = tmp.footprint;
@@ -1329,7 +1332,7 @@ int jc_footprint_rectilinear(const int64_t grid[3], const int64_t* const cuts[3]
     if (!bytes)
         return fail(JC_ERR_INVALID, "bytes must not be NULL");
     jc_ctx tmp;
-    int st = rect_geometry(&tmp, grid, cuts, ncuts, opt);
+    int st = rect_geometry(&tmp, false, grid, cuts, ncuts, opt);
     if (st != JC_OK)
         return st;
     *bytes = tmp.footprint;
@@ -1344,7 +1347,7 @@ int jc_create(const int64_t grid[3], const int64_t block_dims[3], const jc_optio
     jc_ctx* c = new (std::nothrow) jc_ctx();
     if (!c)
         return fail(JC_ERR_NOMEM, "host allocation failed");
-    int st = uniform_geometry(c, grid, block_dims, opt);
+    int st = uniform_geometry(c, true, grid, block_dims, opt);
     if (st != JC_OK) {
         delete c;
         return st;
@@ -1362,7 +1365,7 @@ int jc_create_rectilinear(const int64_t grid[3], const int64_t* const cuts[3], c
     jc_ctx* c = new (std::nothrow) jc_ctx();
     if (!c)
         return fail(JC_ERR_NOMEM, "host allocation failed");
-    int st = rect_geometry(c, grid, cuts, ncuts, opt);
+    int st = rect_geometry(c, true, grid, cuts, ncuts, opt);
     if (st != JC_OK) {
         delete c;
         return st;
