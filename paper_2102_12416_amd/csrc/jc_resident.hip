@@ -35,8 +35,8 @@
 //    while the vector units do.
 // Measured on MI355X, us per sweep without / with a source (before: addresses
 // computed per read, each step's LDS, barrier and arithmetic in a row): 32^3
-// 6.95 / 9.0 -> 6.1 / 6.8, 16^3 2.60 / 3.24 -> 1.98 / 2.12, 8^3 1.17 / 1.53 ->
-// 0.93 / 1.00; 1024 grids of 32^3 855 -> 1050 GLUP/s with a source.  Per step of
+// 6.95 / 9.0 -> 6.05 / 6.8, 16^3 2.60 / 3.24 -> 2.03 / 2.25, 8^3 1.17 / 1.53 ->
+// 0.90 / 0.99; 1024 grids of 32^3 822 -> 1017 GLUP/s with a source.  Per step of
 // 32^3 LDS works 568 of 920 cycles and each SIMD issues for 420; what is left is
 // the chain from a step's first add to its last write and the barrier.
 // A buffer is written two steps after it was read, with a barrier between.
@@ -341,7 +341,7 @@ k_resident(const BlockDesc* __restrict__ blocks, const Item* __restrict__ items,
     // With two waves on a SIMD (STAGGER: more than 256 pairs) one uses LDS before
     // it computes and the other after: issue is in order, so with all waves at
     // LDS first the vector units would wait for its queue (32^3: 6.1 us per
-    // sweep against 7.1).  Fewer waves only lose by it (16^3: 2.18 against 1.98).
+    // sweep against 7.1).  Fewer waves only lose by it (16^3: 10 %).
     const bool early = !STAGGER || (__builtin_amdgcn_readfirstlane(t) & 256) == 0;
     auto up = [&](auto ic) __attribute__((always_inline)) -> bool {
         constexpr int I = decltype(ic)::value;
